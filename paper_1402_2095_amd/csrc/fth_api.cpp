@@ -48,6 +48,7 @@ uint64_t hash_words(const void* p, size_t bytes, uint64_t seed) {
 
 constexpr int kDefaultGraphSteps = 64;
 constexpr int kTbMaxSteps = 5;   // longest temporally blocked launch (snapshot depth)
+constexpr int64_t kReadChunk = 32768;  // estimates per readout chunk (16 bytes each; two chunks are kept pinned)
 constexpr int64_t kTbMaxW = 16;  // widest half-bandwidth blocked
 
 bool is_pow2(int64_t x) { return x > 0 && (x & (x - 1)) == 0; }
@@ -1283,25 +1284,46 @@ fth_status fth_read(fth_ctx* c, double* est, double* se, int64_t len, int64_t* n
     if (!c) return fail(FTH_EINVAL, "ctx must not be NULL");
     const int64_t no = c->n_out();
     if (len < no) return fail(FTH_EINVAL, "output length %lld < %lld", (long long)len, (long long)no);
-    std::vector<double> blk(no), s1(no), s2(no);
-    int64_t nb = 0, step = 0;
-    fth_status st = fth_get_accumulators(c, blk.data(), s1.data(), s2.data(), &nb, &step);
-    if (st != FTH_OK) return st;
-    const int64_t nacc = std::max<int64_t>(0, step - c->opt.burn_in);
+    const int64_t nacc = std::max<int64_t>(0, c->step - c->opt.burn_in);
     const double R = c->R > 0 ? double(c->R) : 1.0;
-    const double L = double(c->opt.block_len);
-    for (int64_t k = 0; k < no; ++k) {
-        if (est) est[k] = nacc > 0 ? (s1[k] + blk[k]) / (R * double(nacc)) : std::numeric_limits<double>::quiet_NaN();
-        if (se) {
-            if (nb < 2) {
-                se[k] = std::numeric_limits<double>::infinity();
-            } else {
-                const double sc = 1.0 / (R * L);
-                const double sb = s1[k] * sc, sbb = s2[k] * sc * sc;
-                const double var = (sbb - sb * sb / double(nb)) / double(nb - 1);
-                se[k] = std::sqrt(std::max(var, 0.0) / double(nb));
-            }
+    fth::ReadScale rs{};
+    rs.samples = R * double(nacc);
+    rs.blocks = double(nacc / c->opt.block_len);
+    rs.per_block = 1.0 / (R * double(c->opt.block_len));
+    HIP_OK(hipSetDevice(c->device));
+    HIP_OK(hipStreamSynchronize(c->stream));
+    // Two chunks in flight: the device forms one while the host copies the other out.
+    if (!c->h_read && no > 0) {
+        const int64_t chunk = std::min(no, kReadChunk);
+        HIP_OK(hipHostMalloc(reinterpret_cast<void**>(&c->h_read), sizeof(double) * 4 * size_t(chunk),
+                             hipHostMallocDefault));
+        c->read_chunk = chunk;
+    }
+    const int64_t ch = c->read_chunk;
+    const hipEvent_t done[2] = {c->ev0, c->ev1};
+    auto form = [&](int64_t j) -> fth_status {
+        double* dst = c->h_read + 2 * ch * (j & 1);
+        const int64_t k0 = j * ch;
+        if (fth::launch_read_estimates(c->d_acc, no, k0, std::min(ch, no - k0), rs, dst, dst + ch, c->stream) != 0)
+            return fail(FTH_EDEVICE, "readout launch failed: %s", hipGetErrorString(hipGetLastError()));
+        HIP_OK(hipEventRecord(done[j & 1], c->stream));
+        return FTH_OK;
+    };
+    const int64_t nch = no > 0 ? (no + ch - 1) / ch : 0;
+    if (nch > 0) {
+        fth_status st = form(0);
+        if (st != FTH_OK) return st;
+    }
+    for (int64_t j = 0; j < nch; ++j) {
+        if (j + 1 < nch) {
+            fth_status st = form(j + 1);
+            if (st != FTH_OK) return st;
         }
+        HIP_OK(hipEventSynchronize(done[j & 1]));
+        const double* src = c->h_read + 2 * ch * (j & 1);
+        const size_t bytes = sizeof(double) * size_t(std::min(ch, no - j * ch));
+        if (est) std::memcpy(est + j * ch, src, bytes);
+        if (se) std::memcpy(se + j * ch, src + ch, bytes);
     }
     if (nsamples) *nsamples = nacc;
     return FTH_OK;

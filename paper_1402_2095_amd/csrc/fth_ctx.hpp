@@ -49,6 +49,8 @@ struct fth_ctx {
                                          // rows grouped by 2^ps_lg (see ps_offset)
     int ps_lg = 0;         // log2 of rows per (p, s) group
     int64_t ps_rows = 0;   // n rounded up to whole groups
+    double* h_read = nullptr;  // pinned: two readout chunks of [est | se][read_chunk]
+    int64_t read_chunk = 0;
     double* d_acc = nullptr;  // [3][n_out]: blk, s1, s2 (pairs first, then diagonal)
     int64_t* d_step = nullptr;
     int32_t* d_flag = nullptr;
@@ -102,6 +104,7 @@ struct fth_ctx {
         if (ev1) (void)hipEventDestroy(ev1);
         if (stream) (void)hipStreamSynchronize(stream);
         for (void* p : allocs) raw_free(p);
+        if (h_read) (void)hipHostFree(h_read);
         if (stream) (void)hipStreamDestroy(stream);
     }
 

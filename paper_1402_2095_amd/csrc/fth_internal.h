@@ -233,6 +233,15 @@ int launch_tb_slots(const int64_t* row_ptr, const int32_t* col, const Real* val,
 int launch_packed_csr(const StepArgs<float>* table, const PackedTile* tiles, const int32_t* ntiles, int ns, bool nt,
                       int grid, int k, void* stream);
 int launch_advance_all(const StepArgs<float>* table, const int32_t* nslots, int64_t K, void* stream);
+// Scales of a readout: samples = R n_acc (0: no sample yet), blocks = complete
+// blocks, per_block = 1 / (R block_len).
+struct ReadScale {
+    double samples, blocks, per_block;
+};
+// Means and standard errors of estimates k0 .. k0 + count - 1 of acc [3][no]
+// (block sums, sums, sums of squares) into est and se (pinned host memory).
+int launch_read_estimates(const double* acc, int64_t no, int64_t k0, int64_t count, const ReadScale& rs, double* est,
+                          double* se, void* stream);
 // One workgroup advances a small dense system by K steps (and the step counter).
 template <typename Real>
 int launch_small_dense(const StepArgs<Real>& a, const StepLaunch& L, int K, size_t lds_bytes, void* stream);

@@ -265,8 +265,8 @@ def fth_num_outputs(ctx) -> int:
 
 def fth_read(ctx):
     n = fth_num_outputs(ctx)
-    est = np.zeros(n)
-    se = np.zeros(n)
+    est = np.empty(n)
+    se = np.empty(n)
     ns = ctypes.c_int64()
     _check(lib().fth_read(ctx, _p(est), _p(se), n, ctypes.byref(ns)))
     return est, se, int(ns.value)
