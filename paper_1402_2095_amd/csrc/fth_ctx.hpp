@@ -42,6 +42,8 @@ struct fth_ctx {
     void* d_msmall = nullptr;
     size_t small_lds = 0;
     int small_m_in_lds = 0;
+    bool small_quad = false;  // small system of at most kSmallQuadRows rows: M in registers, estimates from d_traj
+    void* d_traj[3] = {nullptr, nullptr, nullptr};  // q, p, M q of a chunk of steps, [kSmallQuadSteps][n][R]
     std::vector<double> m_host;  // dense M kept until R fixes the path (n <= 4096)
     bool m_uploaded = false;
     void* d_q[2] = {nullptr, nullptr};

@@ -246,6 +246,30 @@ int launch_read_estimates(const double* acc, int64_t no, int64_t k0, int64_t cou
 template <typename Real>
 int launch_small_dense(const StepArgs<Real>& a, const StepLaunch& L, int K, size_t lds_bytes, void* stream);
 
+// Trajectory of a chunk of steps of a small dense system, [K][N][R] each: q_n,
+// p_n (null unless momentum-form or trace estimates are kept) and M q_n (null
+// unless traces are kept).
+template <typename Real>
+struct SmallTraj {
+    Real* q;
+    Real* p;
+    Real* f;
+};
+// Small dense systems of at most kSmallQuadRows rows: a quad of lanes per row with
+// its row of M in registers (small_quad.hpp).  The limit is the 512 threads at
+// which a thread may hold 32 columns in FP64 besides its state.
+constexpr int kSmallQuadRows = 128;
+// Steps per launch: bounds the trajectory buffer at 8 MB per kind (n R <= 4096 in FP64).
+constexpr int kSmallQuadSteps = 256;
+constexpr size_t small_quad_lds(int64_t n, int R, int ns, bool f64) {
+    const size_t rr = R < 4 ? size_t(R) : 4, d = size_t(ns) + 1;
+    const size_t rows = size_t(n * 4 + 63) / 64 * 16, cols = n <= 64 ? 64 : 128;
+    return (2 * cols * rr + 4 * d * rows * rr + 2 * d * d) * (f64 ? 8 : 4);
+}
+// K <= kSmallQuadSteps steps and their estimates; the step counter is left as it is.
+template <typename Real>
+int launch_small_quad(const StepArgs<Real>& a, const SmallTraj<Real>& tj, int K, void* stream);
+
 // Host FP64 linear algebra (fth_linalg.cpp).
 namespace la {
 // exp(A) for an n x n row-major matrix (scaling and squaring with a

@@ -1,0 +1,9 @@
+// FP64 instantiations of the small-system kernel with M in registers.
+#include "small_quad.hpp"
+
+namespace fth {
+template <>
+int launch_small_quad<double>(const StepArgs<double>& a, const SmallTraj<double>& tj, int K, void* stream) {
+    return launch_small_quad_impl<double>(a, tj, K, stream);
+}
+}  // namespace fth
