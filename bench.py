@@ -48,7 +48,7 @@ KERNEL_SOURCES = {
     "tb": ["tb_step.hpp", "tb_step.hip", "row_update.hpp", "noise.hpp"],
     "tbp": ["tbp_step.hpp", "tbp_step.hip", "tb_step.hpp", "row_update.hpp", "noise.hpp"],
     "dense": ["dense.hpp", "dense_f32.hip", "dense_f64.hip", "row_update.hpp", "noise.hpp"],
-    "gemv": ["dense_gemv.hip", "dense.hpp", "dense_f32.hip", "row_update.hpp", "noise.hpp"],
+    "gemv": ["dense_gemv.hpp", "dense_gemv_f32.hip", "row_update.hpp", "noise.hpp"],
 }
 
 
@@ -204,6 +204,10 @@ def unit_of(kernel_name: str):
         gemm, rt, real, ns, rpt, nt = m.groups()
         return "dense", [f"{gemm}<{rt}>", f"dense_epilogue_kernel<{real}, {ns}, {rpt}, "
                                           f"{'true' if nt == '1' else 'false'},"], 1
+    m = re.search(r"dense_gemv_kernel<(\w+),NS=(\d+),R=(\d+)>", kernel_name)
+    if m:
+        real, ns, r = m.groups()
+        return "gemv", [f"dense_gemv_kernel<{real}, {ns}, {r}>"], 1
     m = re.search(r"dense_gemv_kernel<(\w+),R=(\d+)> \+ dense_epilogue_kernel<(\w+),NS=(\d+),RPT=(\d+),NT=(\d)>",
                   kernel_name)
     if m:
@@ -296,7 +300,7 @@ def roofline(w: dict, r: dict, steps: int) -> dict:
                              "tbp": f"one blocked launch = {r['unit_steps']} steps (persistent step kernel "
                                     "+ pair kernel)",
                              "dense": "one step (GEMM + epilogue launches)",
-                             "gemv": "one step (matrix-vector + epilogue launches)"}.get(r["kind"], "one step"),
+                             "gemv": "one step (matrix-vector launch)"}.get(r["kind"], "one step"),
             "kernels": r["kernels"], "algorithmic_bytes_per_unit": abytes,
             "algorithmic_bytes_per_replica_dof_step": sb / (w["n"] * w["R"]), "avg_unit_us": per_unit_s * 1e6}
     if cnt:

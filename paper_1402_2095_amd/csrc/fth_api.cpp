@@ -466,11 +466,11 @@ fth_status ensure_state(fth_ctx* c, int32_t R) {
         if (c->opt.acc_pp || c->opt.acc_trace) HIP_OK(c->dalloc(&c->d_traj[1], tb));
         if (c->opt.acc_trace) HIP_OK(c->dalloc(&c->d_traj[2], tb));
     }
-    if (c->mfma()) {
+    if (c->mfma() && !c->gemv) {
         const size_t pb = size_t(c->ksplit) * size_t(c->rows_pad) * size_t(R) * rb;
         HIP_OK(c->dalloc(&c->d_part, pb));
         HIP_OK(hipMemsetAsync(c->d_part, 0, pb, c->stream));
-        if (c->prec == FTH_FP32_BF16X3 && !c->gemv) {
+        if (c->prec == FTH_FP32_BF16X3) {
             const size_t qtb = size_t(c->rows_pad) * size_t(R) * 2 * sizeof(uint16_t);
             HIP_OK(c->dalloc(reinterpret_cast<void**>(&c->d_qt), qtb));
             HIP_OK(hipMemsetAsync(c->d_qt, 0, qtb, c->stream));
@@ -579,20 +579,30 @@ fth::DenseGemmArgs gemm_args(fth_ctx* c, int k) {
     return g;
 }
 
-// The dense force partials of one step: the matrix-core GEMM, or for R < 16
+// The dense force partials of q_0 of g: the matrix-core GEMM, or for R < 16
 // the matrix-vector form.
 int launch_force(const fth_ctx* c, const fth::DenseGemmArgs& g) {
     if (c->gemv)
         return c->prec == FTH_FP64
-                   ? fth::launch_dense_gemv<double>(g, static_cast<const double*>(c->d_m_hi), c->n, c->rows_pad, c->stream)
-                   : fth::launch_dense_gemv<float>(g, static_cast<const float*>(c->d_m_hi), c->n, c->rows_pad, c->stream);
+                   ? fth::launch_gemv_force<double>(static_cast<const double*>(c->d_m_hi), c->rows_pad, c->n, c->R,
+                                                    static_cast<const double*>(g.q0), static_cast<double*>(g.part),
+                                                    c->stream)
+                   : fth::launch_gemv_force<float>(static_cast<const float*>(c->d_m_hi), c->rows_pad, c->n, c->R,
+                                                   static_cast<const float*>(g.q0), static_cast<float*>(g.part),
+                                                   c->stream);
     return c->prec == FTH_FP64 ? fth::launch_gemm_f64(g, c->stream) : fth::launch_gemm_bf16x3(g, c->stream);
 }
 
 // Enqueue one step with in-chunk offset k (global step = *d_step + k).
 fth_status enqueue_step(fth_ctx* c, int k) {
     int rc;
-    if (c->dense()) {
+    if (c->gemv) {
+        rc = c->prec == FTH_FP64
+                 ? fth::launch_dense_gemv<double>(step_args<double>(c), static_cast<const double*>(c->d_m_hi),
+                                                  c->rows_pad, k, c->stream)
+                 : fth::launch_dense_gemv<float>(step_args<float>(c), static_cast<const float*>(c->d_m_hi), c->rows_pad,
+                                                 k, c->stream);
+    } else if (c->dense()) {
         const fth::DenseGemmArgs g = gemm_args(c, k);
         rc = launch_force(c, g);
         if (rc != 0) return fail(FTH_EDEVICE, "dense force launch failed (%d)", rc);
@@ -613,6 +623,10 @@ fth_status enqueue_step(fth_ctx* c, int k) {
 // Rows of the widest tiling the current shape launches (one-step, blocked or small).
 int64_t trace_tiles(const fth_ctx* c) {
     if (c->small) return 1;
+    if (c->gemv) {
+        const int rows = fth::gemv_rows(c->prec == FTH_FP64, c->R);
+        return (c->n + rows - 1) / rows;
+    }
     const int per_block = c->block / (c->R / c->rpt);
     int64_t w = (c->n + per_block - 1) / per_block;
     if (c->tb_kt > 0) {
@@ -1077,7 +1091,6 @@ size_t fth_footprint_bytes(const fth_matrix* M, int32_t ns, int32_t R, int64_t n
         const size_t ld = (n + 3) / 4 * 4;                                    // matrix-vector form
         bytes += n * ld * rb;                                                  // M
         bytes += 2 * ld * size_t(R) * rb + 2 * ps_rows * size_t(R) * rb * size_t(1 + ns);
-        bytes += ld * size_t(R) * rb;                                          // force partials
     } else {
         const size_t P = size_t(dense_rows_pad(int64_t(n)));
         const size_t ks = size_t(dense_ksplit(int64_t(P), precision));
@@ -1494,7 +1507,7 @@ fth_status fth_force(fth_ctx* c, const double* q, double* F) {
 
 double fth_last_run_ms(const fth_ctx* c) { return c ? c->last_ms : 0.0; }
 
-int32_t fth_launches_per_step(const fth_ctx* c) { return c ? (c->mfma() ? 2 : 1) : 0; }
+int32_t fth_launches_per_step(const fth_ctx* c) { return c ? (c->mfma() && !c->gemv ? 2 : 1) : 0; }
 
 fth_status fth_kernel_name(const fth_ctx* c, char* name, size_t len) {
     if (!c || !name || len == 0) return fail(FTH_EINVAL, "invalid arguments");
@@ -1505,9 +1518,7 @@ fth_status fth_kernel_name(const fth_ctx* c, char* name, size_t len) {
         std::snprintf(name, len, "small_dense_kernel<%s,NS=%d,RPT=%d> (persistent, M in %s)",
                       c->prec == FTH_FP64 ? "double" : "float", c->ns, c->rpt, c->small_m_in_lds ? "LDS" : "global");
     else if (c->gemv)
-        std::snprintf(name, len, "dense_gemv_kernel<%s,R=%d> + dense_epilogue_kernel<%s,NS=%d,RPT=%d,NT=%d>",
-                      c->prec == FTH_FP64 ? "double" : "float", c->R, c->prec == FTH_FP64 ? "double" : "float", c->ns,
-                      c->rpt, int(c->nt));
+        std::snprintf(name, len, "dense_gemv_kernel<%s,NS=%d,R=%d>", c->prec == FTH_FP64 ? "double" : "float", c->ns, c->R);
     else if (c->dense())
         std::snprintf(name, len, "%s<RT=%d,ksplit=%d> + dense_epilogue_kernel<%s,NS=%d,RPT=%d,NT=%d>",
                       c->prec == FTH_FP64 ? "gemm_f64_kernel" : "gemm_bf16x3_kernel", c->R / 16, c->ksplit,

@@ -201,10 +201,18 @@ template <typename Real>
 int launch_dense_epilogue(const StepArgs<Real>& a, const StepLaunch& L, int k, void* stream);
 int launch_gemm_bf16x3(const DenseGemmArgs& g, void* stream);
 int launch_gemm_f64(const DenseGemmArgs& g, void* stream);
-// Dense force for R in {1, 2, 4, 8}: part[i][r] = (M q_n)_ir with M row-major [N][ld]
-// (ld a multiple of 4, >= N, <= g.rows_pad) in the state precision.
+// One dense step for R in {1, 2, 4, 8} (in-chunk offset k): the force as matrix-vector
+// products in the state precision, M row-major [N][ld] (ld a multiple of 4, >= N), and
+// the row update, one launch.
 template <typename Real>
-int launch_dense_gemv(const DenseGemmArgs& g, const Real* M, int64_t N, int64_t ld, void* stream);
+int launch_dense_gemv(const StepArgs<Real>& a, const Real* M, int64_t ld, int k, void* stream);
+// Its force alone: part[i][r] = (M q)_ir.
+template <typename Real>
+int launch_gemv_force(const Real* M, int64_t ld, int64_t N, int R, const Real* q, Real* part, void* stream);
+// Rows per workgroup of the dense matrix-vector step (its trace partials are per
+// workgroup).  At 8 FP32 replicas q_n costs as many bytes from L2 as 8 rows of M, so
+// sixteen rows share it.
+constexpr int gemv_rows(bool f64, int R) { return !f64 && R == 8 ? 16 : 8; }
 // M [P][P] FP32 -> bf16 hi/lo parts in the split GEMM's tiled layout (4 P^2 bytes at mt).
 int launch_split_bf16_tiled(const float* m, void* mt, int64_t P, void* stream);
 int launch_qt_from_q(const float* q, uint16_t* qt, int64_t N, int64_t rows_pad, int32_t R, void* stream);
