@@ -48,6 +48,7 @@ KERNEL_SOURCES = {
     "tb": ["tb_step.hpp", "tb_step.hip", "row_update.hpp", "noise.hpp"],
     "tbp": ["tbp_step.hpp", "tbp_step.hip", "tb_step.hpp", "row_update.hpp", "noise.hpp"],
     "dense": ["dense.hpp", "dense_f32.hip", "dense_f64.hip", "row_update.hpp", "noise.hpp"],
+    "rows": ["dense_rows.hpp", "dense_rows_f32.hip", "dense_rows_f64.hip", "dense.hpp", "row_update.hpp", "noise.hpp"],
     "gemv": ["dense_gemv.hpp", "dense_gemv_f32.hip", "row_update.hpp", "noise.hpp"],
 }
 
@@ -204,6 +205,9 @@ def unit_of(kernel_name: str):
         gemm, rt, real, ns, rpt, nt = m.groups()
         return "dense", [f"{gemm}<{rt}>", f"dense_epilogue_kernel<{real}, {ns}, {rpt}, "
                                           f"{'true' if nt == '1' else 'false'},"], 1
+    m = re.search(r"(dense_rows_bf16x3_kernel|dense_rows_f64_kernel)<NS=(\d+),CT=(\d+)>", kernel_name)
+    if m:
+        return "rows", [f"{m.group(1)}<{m.group(2)}, {m.group(3)}>"], 1
     m = re.search(r"dense_gemv_kernel<(\w+),NS=(\d+),R=(\d+)>", kernel_name)
     if m:
         real, ns, r = m.groups()

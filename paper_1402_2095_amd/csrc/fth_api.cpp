@@ -305,6 +305,25 @@ int dense_ksplit(int64_t P, int prec) {
     return ks;
 }
 
+// 16-column tiles per workgroup of the one-launch dense step, 0 where the GEMM with its
+// epilogue is the faster form.  Every workgroup of the one-launch form reads its columns
+// of all of q_n from L2, n^2 R / 16 values a step at 16 rows each, against two launches
+// and the partial sums of the GEMM form.  Measured, us per step, one launch against GEMM:
+//   split form  n = 520 R = 64 4.6 / 10.8, 1000 R = 128 6.4 / 14.8, 2100 R = 64 13.0 / 15.1,
+//               4000 R = 16 15.2 / 15.9, 2100 R = 128 21.2 / 21.8, 4000 R = 32 19.3 / 17.7
+//   FP64        n = 520 R = 64 7.0 / 19.3, 1000 R = 64 10.2 / 19.8, 2100 R = 16 19.9 / 22.9,
+//               2100 R = 32 25.7 / 24.8
+// so the line lies at n^2 R = 3.2e8 (split) and 1e8 (FP64).  As few column tiles as keep
+// the launch within one workgroup per CU: more of them read M again, fewer leave CUs idle
+// (1000 rows, R = 64: 5.2 us with one tile, 252 workgroups; 7.0 with four, 63).
+int dense_rows_cols(int64_t n, int R, int prec) {
+    if (R != 16 && R != 32 && R != 64 && R != 128) return 0;
+    if (double(n) * double(n) * R > (prec == FTH_FP64 ? 1.0e8 : 3.2e8)) return 0;
+    int ct = 1;
+    while (ct < 4 && 16 * ct < R && (n + 15) / 16 * (R / (16 * ct)) > 256) ct *= 2;
+    return ct;
+}
+
 // Dense M padded to rows_pad x rows_pad with zeros: bf16 hi/lo split on the
 // device for the split form, FP64 as is.
 fth_status upload_dense(fth_ctx* c, const std::vector<double>& M) {
@@ -467,13 +486,20 @@ fth_status ensure_state(fth_ctx* c, int32_t R) {
         if (c->opt.acc_trace) HIP_OK(c->dalloc(&c->d_traj[2], tb));
     }
     if (c->mfma() && !c->gemv) {
-        const size_t pb = size_t(c->ksplit) * size_t(c->rows_pad) * size_t(R) * rb;
-        HIP_OK(c->dalloc(&c->d_part, pb));
-        HIP_OK(hipMemsetAsync(c->d_part, 0, pb, c->stream));
+        c->rows_ct = dense_rows_cols(c->n, R, c->prec);
+        if (c->rows_ct == 0) {
+            const size_t pb = size_t(c->ksplit) * size_t(c->rows_pad) * size_t(R) * rb;
+            HIP_OK(c->dalloc(&c->d_part, pb));
+            HIP_OK(hipMemsetAsync(c->d_part, 0, pb, c->stream));
+        }
         if (c->prec == FTH_FP32_BF16X3) {
             const size_t qtb = size_t(c->rows_pad) * size_t(R) * 2 * sizeof(uint16_t);
             HIP_OK(c->dalloc(reinterpret_cast<void**>(&c->d_qt), qtb));
             HIP_OK(hipMemsetAsync(c->d_qt, 0, qtb, c->stream));
+            if (c->rows_ct > 0) {
+                HIP_OK(c->dalloc(reinterpret_cast<void**>(&c->d_qt2), qtb));
+                HIP_OK(hipMemsetAsync(c->d_qt2, 0, qtb, c->stream));
+            }
             c->qt_dirty = true;
         }
     }
@@ -602,6 +628,10 @@ fth_status enqueue_step(fth_ctx* c, int k) {
                                                   c->rows_pad, k, c->stream)
                  : fth::launch_dense_gemv<float>(step_args<float>(c), static_cast<const float*>(c->d_m_hi), c->rows_pad,
                                                  k, c->stream);
+    } else if (c->rows_ct > 0) {
+        const fth::DenseRowsArgs g{c->d_m_hi, c->d_qt, c->d_qt2, c->rows_pad, 0, 0, 0};
+        rc = c->prec == FTH_FP64 ? fth::launch_dense_rows<double>(step_args<double>(c), g, c->rows_ct, k, c->stream)
+                                 : fth::launch_dense_rows<float>(step_args<float>(c), g, c->rows_ct, k, c->stream);
     } else if (c->dense()) {
         const fth::DenseGemmArgs g = gemm_args(c, k);
         rc = launch_force(c, g);
@@ -627,6 +657,7 @@ int64_t trace_tiles(const fth_ctx* c) {
         const int rows = fth::gemv_rows(c->prec == FTH_FP64, c->R);
         return (c->n + rows - 1) / rows;
     }
+    if (c->rows_ct > 0) return (c->n + 15) / 16 * (c->R / (16 * c->rows_ct));
     const int per_block = c->block / (c->R / c->rpt);
     int64_t w = (c->n + per_block - 1) / per_block;
     if (c->tb_kt > 0) {
@@ -1010,7 +1041,8 @@ fth_status run_enqueue(fth_ctx* c, int64_t nsteps) {
     st = trace_prepare(c, c->small ? 4096 : K);
     if (st != FTH_OK) return st;
     if (c->d_qt && c->qt_dirty) {
-        if (fth::launch_qt_from_q(static_cast<const float*>(c->d_q[c->step & 1]), c->d_qt, c->n, c->rows_pad, c->R,
+        uint16_t* qt = c->rows_ct > 0 && (c->step & 1) ? c->d_qt2 : c->d_qt;
+        if (fth::launch_qt_from_q(static_cast<const float*>(c->d_q[c->step & 1]), qt, c->n, c->rows_pad, c->R,
                                   c->stream) != 0)
             return fail(FTH_EDEVICE, "q split launch failed");
         c->qt_dirty = false;
@@ -1096,8 +1128,9 @@ size_t fth_footprint_bytes(const fth_matrix* M, int32_t ns, int32_t R, int64_t n
         const size_t ks = size_t(dense_ksplit(int64_t(P), precision));
         bytes += P * P * (precision == FTH_FP32_BF16X3 ? 4 : rb);           // M (hi + lo, or FP64)
         bytes += 2 * P * size_t(R) * rb + 2 * ps_rows * size_t(R) * rb * size_t(1 + ns);  // q, (p, s) pairs
-        bytes += ks * P * size_t(R) * rb;                                      // split-K partials
-        if (precision == FTH_FP32_BF16X3) bytes += P * size_t(R) * 4;          // bf16 q split
+        const bool rows = dense_rows_cols(int64_t(n), R, precision) > 0;
+        if (!rows) bytes += ks * P * size_t(R) * rb;                           // split-K partials
+        if (precision == FTH_FP32_BF16X3) bytes += P * size_t(R) * (rows ? 8 : 4);  // bf16 q split(s)
     }
     const size_t nout = size_t(npairs) + (acc_diag ? n : 0);
     bytes += nout * 24 + size_t(npairs) * 8;
@@ -1507,7 +1540,7 @@ fth_status fth_force(fth_ctx* c, const double* q, double* F) {
 
 double fth_last_run_ms(const fth_ctx* c) { return c ? c->last_ms : 0.0; }
 
-int32_t fth_launches_per_step(const fth_ctx* c) { return c ? (c->mfma() && !c->gemv ? 2 : 1) : 0; }
+int32_t fth_launches_per_step(const fth_ctx* c) { return c ? (c->mfma() && !c->gemv && c->rows_ct == 0 ? 2 : 1) : 0; }
 
 fth_status fth_kernel_name(const fth_ctx* c, char* name, size_t len) {
     if (!c || !name || len == 0) return fail(FTH_EINVAL, "invalid arguments");
@@ -1519,6 +1552,9 @@ fth_status fth_kernel_name(const fth_ctx* c, char* name, size_t len) {
                       c->prec == FTH_FP64 ? "double" : "float", c->ns, c->rpt, c->small_m_in_lds ? "LDS" : "global");
     else if (c->gemv)
         std::snprintf(name, len, "dense_gemv_kernel<%s,NS=%d,R=%d>", c->prec == FTH_FP64 ? "double" : "float", c->ns, c->R);
+    else if (c->rows_ct > 0)
+        std::snprintf(name, len, "%s<NS=%d,CT=%d> R=%d",
+                      c->prec == FTH_FP64 ? "dense_rows_f64_kernel" : "dense_rows_bf16x3_kernel", c->ns, c->rows_ct, c->R);
     else if (c->dense())
         std::snprintf(name, len, "%s<RT=%d,ksplit=%d> + dense_epilogue_kernel<%s,NS=%d,RPT=%d,NT=%d>",
                       c->prec == FTH_FP64 ? "gemm_f64_kernel" : "gemm_bf16x3_kernel", c->R / 16, c->ksplit,

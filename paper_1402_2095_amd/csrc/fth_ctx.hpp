@@ -35,6 +35,8 @@ struct fth_ctx {
     void* d_m_hi = nullptr;
     void* d_part = nullptr;
     uint16_t* d_qt = nullptr;
+    uint16_t* d_qt2 = nullptr;  // one-launch form: the split of q at odd steps (d_qt: even steps)
+    int rows_ct = 0;            // one-launch form: 16-column tiles per workgroup, 0: GEMM and epilogue
     bool qt_dirty = true;
     // small dense systems: persistent single-workgroup kernel, M [n][n] in state precision
     bool small = false;

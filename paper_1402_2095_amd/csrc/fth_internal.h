@@ -201,6 +201,21 @@ template <typename Real>
 int launch_dense_epilogue(const StepArgs<Real>& a, const StepLaunch& L, int k, void* stream);
 int launch_gemm_bf16x3(const DenseGemmArgs& g, void* stream);
 int launch_gemm_f64(const DenseGemmArgs& g, void* stream);
+// One dense step for R in {16, 32, 64, 128} in one launch (dense_rows.hpp): workgroups
+// of 16 rows and 16 ct columns.  m, rows_pad and the q split are the GEMM's; the split
+// is double-buffered (step n reads qt0 for even n, qt1 for odd n and writes the other;
+// both null in FP64).  The launcher fills the rest.
+struct DenseRowsArgs {
+    const void* m;
+    uint16_t* qt0;
+    uint16_t* qt1;
+    int64_t rows_pad;
+    int32_t ksteps;
+    int32_t cgroups;
+    int64_t tiles;
+};
+template <typename Real>
+int launch_dense_rows(const StepArgs<Real>& a, const DenseRowsArgs& g, int ct, int k, void* stream);
 // One dense step for R in {1, 2, 4, 8} (in-chunk offset k): the force as matrix-vector
 // products in the state precision, M row-major [N][ld] (ld a multiple of 4, >= N), and
 // the row update, one launch.
