@@ -1553,7 +1553,7 @@ fth_status fth_kernel_name(const fth_ctx* c, char* name, size_t len) {
     else if (c->gemv)
         std::snprintf(name, len, "dense_gemv_kernel<%s,NS=%d,R=%d>", c->prec == FTH_FP64 ? "double" : "float", c->ns, c->R);
     else if (c->rows_ct > 0)
-        std::snprintf(name, len, "%s<NS=%d,CT=%d> R=%d",
+        std::snprintf(name, len, "%s<NS=%d,CT=%d> R=%d (one launch for the GEMM and dense_epilogue_kernel)",
                       c->prec == FTH_FP64 ? "dense_rows_f64_kernel" : "dense_rows_bf16x3_kernel", c->ns, c->rows_ct, c->R);
     else if (c->dense())
         std::snprintf(name, len, "%s<RT=%d,ksplit=%d> + dense_epilogue_kernel<%s,NS=%d,RPT=%d,NT=%d>",
