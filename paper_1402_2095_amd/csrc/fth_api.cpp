@@ -569,7 +569,7 @@ fth::StepArgs<Real> step_args(fth_ctx* c) {
             a.dp_s2 = s2 + o + c->npairs;
         }
     }
-    a.flag = c->d_flag;
+    a.flag = c->h_flag;
     a.tpart = c->opt.acc_trace ? c->d_tpart : nullptr;
     a.tpart_w = c->tpart_w;
     const int per_block = c->block / (c->R / c->rpt);
@@ -1013,8 +1013,8 @@ fth_status autotune(fth_ctx* c) {
     // restore
     for (int k = 0; k < 4; ++k) HIP_OK(hipMemcpyAsync(bufs[k], saved[k], sizes[k], hipMemcpyDeviceToDevice, c->stream));
     HIP_OK(hipMemcpyAsync(c->d_step, &step0, sizeof(int64_t), hipMemcpyHostToDevice, c->stream));
-    HIP_OK(hipMemsetAsync(c->d_flag, 0, sizeof(int32_t), c->stream));
     HIP_OK(hipStreamSynchronize(c->stream));
+    *c->h_flag = 0;
     c->block = best.block;
     c->rpt = best.rpt;
     c->nt = best.nt;
@@ -1069,9 +1069,7 @@ fth_status run_enqueue(fth_ctx* c, int64_t nsteps) {
 fth_status run_complete(fth_ctx* c, int64_t nsteps) {
     HIP_OK(hipStreamSynchronize(c->stream));
     c->step += nsteps;
-    int32_t flag = 0;
-    HIP_OK(hipMemcpy(&flag, c->d_flag, sizeof(flag), hipMemcpyDeviceToHost));
-    if (flag) {
+    if (*static_cast<volatile int32_t*>(c->h_flag) != 0) {
         c->poisoned = true;
         return fail(FTH_ENONFINITE, "non-finite state after step %lld (M not SPD or dt too large)", (long long)c->step);
     }
@@ -1275,8 +1273,8 @@ fth_status fth_create(const fth_matrix* M_in, const fth_gle* gle_in, double dt, 
     HIP_OK(hipMemset(c->d_acc, 0, std::max<size_t>(accb, 8)));
     HIP_OK(c->dalloc(reinterpret_cast<void**>(&c->d_step), sizeof(int64_t)));
     HIP_OK(hipMemset(c->d_step, 0, sizeof(int64_t)));
-    HIP_OK(c->dalloc(reinterpret_cast<void**>(&c->d_flag), sizeof(int32_t)));
-    HIP_OK(hipMemset(c->d_flag, 0, sizeof(int32_t)));
+    HIP_OK(hipHostMalloc(reinterpret_cast<void**>(&c->h_flag), sizeof(int32_t), hipHostMallocDefault));
+    *c->h_flag = 0;
     if (opt.replicas != 0) {
         st = ensure_state(c.get(), opt.replicas);
         if (st != FTH_OK) return st;
@@ -1707,8 +1705,7 @@ fth_status fth_load(fth_ctx* c, const void* buf, size_t len) {
     const size_t ab = sizeof(double) * 3 * size_t(hd.n_out);
     if (ab) HIP_OK(hipMemcpy(c->d_acc, in + off, ab, hipMemcpyHostToDevice));
     HIP_OK(hipMemcpy(c->d_step, &c->step, sizeof(int64_t), hipMemcpyHostToDevice));
-    const int32_t flag = hd.poisoned ? 1 : 0;
-    HIP_OK(hipMemcpy(c->d_flag, &flag, sizeof(flag), hipMemcpyHostToDevice));
+    *c->h_flag = hd.poisoned ? 1 : 0;
     c->poisoned = hd.poisoned != 0;
     c->qt_dirty = true;
     return FTH_OK;

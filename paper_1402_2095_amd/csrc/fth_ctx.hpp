@@ -57,7 +57,7 @@ struct fth_ctx {
     int64_t read_chunk = 0;
     double* d_acc = nullptr;  // [3][n_out]: blk, s1, s2 (pairs first, then diagonal)
     int64_t* d_step = nullptr;
-    int32_t* d_flag = nullptr;
+    int32_t* h_flag = nullptr;  // pinned, written by the kernels, read by the host once they have ended
     // coded sparse form: per row 8 one-byte column / value codes into tables
     bool coded = false;
     uint64_t* d_ell_col = nullptr;    // [n]
@@ -109,6 +109,7 @@ struct fth_ctx {
         if (stream) (void)hipStreamSynchronize(stream);
         for (void* p : allocs) raw_free(p);
         if (h_read) (void)hipHostFree(h_read);
+        if (h_flag) (void)hipHostFree(h_flag);
         if (stream) (void)hipStreamDestroy(stream);
     }
 

@@ -80,7 +80,7 @@ struct StepArgs {
     // replicas of q^2 (c = 0), q (M q) (c = 1) and p^2 (c = 2)
     double* tpart;
     int32_t tpart_w;
-    int32_t* flag;  // set to 1 when a non-finite state value appears
+    int32_t* flag;  // set to 1 when a non-finite state value appears (pinned host memory)
     int32_t ns;     // extra GLE momenta
     // launch geometry
     int64_t row_tiles;         // tiles of rows

@@ -372,9 +372,7 @@ void complete_group(fth_server* s, Group& g) {
         r->info.chunks += 1;
         r->info.device_ms += ms;
         note_span(s, r->info, g.ev0, g.ev1);
-        int32_t flag = 0;
-        if (hipMemcpy(&flag, c->d_flag, sizeof(flag), hipMemcpyDeviceToHost) != hipSuccess) flag = 1;
-        if (flag) {
+        if (*static_cast<volatile int32_t*>(c->h_flag) != 0) {
             c->poisoned = true;
             finish(s, r, FTH_REQ_FAILED,
                    fail(FTH_ENONFINITE, "non-finite state in request %llu", (unsigned long long)r->id));

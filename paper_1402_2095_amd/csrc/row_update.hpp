@@ -74,9 +74,32 @@ __device__ __forceinline__ void acc_update(double* blk, double* s1, double* s2, 
     }
 }
 
+// Value of another lane by a DPP control (a vector move, no LDS round trip).
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+    const uint64_t b = uint64_t(__double_as_longlong(v));
+    const uint32_t lo = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(b)), CTRL, 0xF, 0xF, true));
+    const uint32_t hi = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(b >> 32)), CTRL, 0xF, 0xF, true));
+    return __longlong_as_double(int64_t((uint64_t(hi) << 32) | lo));
+}
+
+// Sum over the tpr consecutive lanes of a row (tpr a power of two), the same in all of
+// them: a butterfly from the nearest lanes outwards.  Once the lanes of a group of 4
+// (8) hold the same value, the mirror of 8 (16) lanes is as good as the exchange at
+// distance 4 (8), so the first four stages need no LDS permute.
 __device__ __forceinline__ double group_sum(double x, int tpr) {
-    for (int off = tpr >> 1; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+    if (tpr > 1) x += dpp_f64<0xB1>(x);   // quad_perm [1,0,3,2]
+    if (tpr > 2) x += dpp_f64<0x4E>(x);   // quad_perm [2,3,0,1]
+    if (tpr > 4) x += dpp_f64<0x141>(x);  // row_half_mirror
+    if (tpr > 8) x += dpp_f64<0x140>(x);  // row_mirror
+    for (int off = 16; off < tpr; off <<= 1) x += __shfl_xor(x, off, 64);
     return x;
+}
+
+// Whether step n (>= burn_in) closes a block.  Steps stay below 2^32, so the
+// remainder is a 32-bit one; longer blocks never close.
+__device__ __forceinline__ bool closes_block(int64_t n, int64_t burn_in, int64_t block_len) {
+    return block_len <= 0xFFFFFFFFll && uint32_t(n - burn_in + 1) % uint32_t(block_len) == 0;
 }
 
 // Per-step constants every launch derives from the device step counter.
@@ -92,7 +115,7 @@ __device__ __forceinline__ StepInfo step_info(const StepArgs<Real>& a, int k) {
     StepInfo s;
     s.n = a.step_base[0] + k;
     s.acc_on = s.n >= a.burn_in;
-    s.close = s.acc_on && ((s.n - a.burn_in + 1) % a.block_len) == 0;
+    s.close = s.acc_on && closes_block(s.n, a.burn_in, a.block_len);
     s.tpr = 1 << a.lg_tpr;
     s.rq = threadIdx.x & (s.tpr - 1);
     s.r0 = s.rq * RPT;
@@ -120,8 +143,9 @@ __device__ __forceinline__ Real* ps_at_step(const StepArgs<Real>& a, int64_t n) 
 template <typename Real, int RPT>
 __device__ __forceinline__ double dot_row(const Vec<Real, RPT>& x, const Vec<Real, RPT>& y, int tpr) {
     double s = 0.0;
+    // (for FP32 state the products are exact in FP64, so the FMA rounds as the sum would)
 #pragma unroll
-    for (int m = 0; m < RPT; ++m) s += double(x.v[m]) * double(y.v[m]);
+    for (int m = 0; m < RPT; ++m) s = __builtin_fma(double(x.v[m]), double(y.v[m]), s);
     return group_sum(s, tpr);
 }
 
@@ -219,7 +243,7 @@ __device__ __forceinline__ void row_traces(const RowState<Real, NS, RPT>& st, co
                                            double (&tr)[3]) {
     double qm = 0.0;
 #pragma unroll
-    for (int m = 0; m < RPT; ++m) qm += double(st.q.v[m]) * double(acc[m]);
+    for (int m = 0; m < RPT; ++m) qm = __builtin_fma(double(st.q.v[m]), double(acc[m]), qm);
     tr[0] = dot_row<Real, RPT>(st.q, st.q, tpr);
     tr[1] = group_sum(qm, tpr);
     tr[2] = dot_row<Real, RPT>(st.p, st.p, tpr);
@@ -292,7 +316,7 @@ __device__ __forceinline__ Vec<Real, RPT> finish_row(const StepArgs<Real>& a, co
 #pragma unroll
     for (int c = 0; c < NS; ++c) store_state<Real, RPT, NT>(psrow + (c + 1) * cs, nx.s[c]);
     store_state<Real, RPT, NT>(qw + i * R + si.r0, nx.q);
-    if (!ok) atomicOr(a.flag, 1);
+    if (!ok) a.flag[0] = 1;
     return nx.q;
 }
 

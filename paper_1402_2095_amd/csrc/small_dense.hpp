@@ -137,7 +137,7 @@ __global__ __launch_bounds__(MAXT) void small_dense_kernel(const StepArgs<Real> 
         const int64_t n = n0 + k;
         double tr[3] = {0.0, 0.0, 0.0};
         const bool acc_on = n >= a.burn_in;
-        const bool close = acc_on && ((n - a.burn_in + 1) % a.block_len) == 0;
+        const bool close = acc_on && closes_block(n, a.burn_in, a.block_len);
         const Real* qr = qb + (n & 1) * N * R;
         Real* qw = qb + ((n + 1) & 1) * N * R;
         // one block-sum update of accumulator slot x in LDS
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(MAXT) void small_dense_kernel(const StepArgs<Real> 
         for (int64_t x = tid; x < np; x += nthr) a.pp_blk[x] = bl[nacc + x];
         for (int64_t x = tid; x < nd; x += nthr) a.dp_blk[x] = bl[nacc + np + x];
     }
-    if (!ok) atomicOr(a.flag, 1);
+    if (!ok) a.flag[0] = 1;
     __syncthreads();
     if (tid == 0) const_cast<int64_t*>(a.step_base)[0] = nend;
 }

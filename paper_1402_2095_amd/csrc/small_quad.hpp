@@ -194,7 +194,7 @@ __global__ __launch_bounds__(512) void small_dense_kernel_quad(const StepArgs<Re
 #pragma unroll
         for (int k = 0; k < NS; ++k) psrow[(k + 1) * cs] = st.s[k].v[0];
     }
-    if (!ok) atomicOr(a.flag, 1);
+    if (!ok) a.flag[0] = 1;
 }
 
 // The estimates of K steps from the trajectory: workgroup (one wave) x takes

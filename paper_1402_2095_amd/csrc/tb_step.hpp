@@ -105,7 +105,7 @@ __global__ __launch_bounds__(tb_max_block(sizeof(Real) == 8, NS, XTRA)) void tb_
     for (int s = 0; s < KT; ++s) {
         const int64_t n = n0 + s;
         const bool acc_on = n >= a.burn_in;
-        const bool close = acc_on && ((n - a.burn_in + 1) % a.block_len) == 0;
+        const bool close = acc_on && closes_block(n, a.burn_in, a.block_len);
         const Real* cur = qlds + int64_t(s & 1) * E * R;
         Real* nxt = qlds + int64_t((s + 1) & 1) * E * R;
         if (output) {
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(tb_max_block(sizeof(Real) == 8, NS, XTRA)) void tb_
         for (int c = 0; c < NS; ++c) store_state<Real, RPT, true>(psrow + (c + 1) * cs, st.s[c]);
         if (a.dblk != nullptr && rq == 0) a.dblk[i] = blk;
         if (XTRA && a.dp_blk != nullptr && rq == 0) a.dp_blk[i] = blkp;
-        if (!ok) atomicOr(a.flag, 1);
+        if (!ok) a.flag[0] = 1;
     }
 }
 
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(256) void tb_pairs_kernel(const StepArgs<Real> a, c
     for (int s = 0; s < KT; ++s) {
         const int64_t n = n0 + s;
         const bool acc_on = n >= a.burn_in;
-        const bool close = acc_on && ((n - a.burn_in + 1) % a.block_len) == 0;
+        const bool close = acc_on && closes_block(n, a.burn_in, a.block_len);
         const Real* sq = tb.snap + int64_t(2 * s) * tb.nslots * R + r0;
         const double x = dot_row<Real, RPT>(load_vec<Real, RPT>(sq + si * R), load_vec<Real, RPT>(sq + sj * R), tpr);
         if (rq == 0 && acc_on) acc_update(a.pblk, a.ps1, a.ps2, pk, x, close);

@@ -207,7 +207,7 @@ __global__ __launch_bounds__(tb_max_block(sizeof(Real) == 8, NS, XTRA)) void tbp
         for (int s = 0; s < KT; ++s) {
             const int64_t n = n0 + s;
             const bool acc_on = n >= a.burn_in;
-            const bool close = acc_on && ((n - a.burn_in + 1) % a.block_len) == 0;
+            const bool close = acc_on && closes_block(n, a.burn_in, a.block_len);
             const Real* cur = qlds + int64_t(s & 1) * E * R;
             Real* nxt = qlds + int64_t((s + 1) & 1) * E * R;
             // the row index as the compiler must treat it in each step: the block
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(tb_max_block(sizeof(Real) == 8, NS, XTRA)) void tbp
             if (XTRA && a.dp_blk != nullptr && rq == 0) a.dp_blk[i] = blkp;
         }
     }
-    if (!ok) atomicOr(a.flag, 1);
+    if (!ok) a.flag[0] = 1;
 }
 
 // Slot form of CSR rows of at most 8 entries (one thread per row).

@@ -32,14 +32,24 @@ __global__ __launch_bounds__(256) void trace_reduce_kernel(double* __restrict__ 
 __global__ void trace_fold_kernel(const double* __restrict__ tsum, int K, int ntr, double* blk, double* s1,
                                   double* s2, const int64_t* step_base, int64_t shift, int64_t burn_in,
                                   int64_t block_len) {
-    if (threadIdx.x != 0) return;
+    const int c = int(threadIdx.x);  // one lane per trace
+    if (c >= ntr) return;
     const int64_t n0 = step_base[0] + shift;
+    double b = blk[c], v1 = s1[c], v2 = s2[c];
     for (int k = 0; k < K; ++k) {
         const int64_t n = n0 + k;
+        const double x = tsum[k * 3 + c];
         if (n < burn_in) continue;
-        const bool close = ((n - burn_in + 1) % block_len) == 0;
-        for (int c = 0; c < ntr; ++c) acc_update(blk, s1, s2, c, tsum[k * 3 + c], close);
+        b = b + x;
+        if (closes_block(n, burn_in, block_len)) {
+            v1 = v1 + b;
+            v2 = v2 + b * b;
+            b = 0.0;
+        }
     }
+    blk[c] = b;
+    s1[c] = v1;
+    s2[c] = v2;
 }
 
 }  // namespace dev
