@@ -9,8 +9,10 @@
 //                                                  relative, is dropped)
 // FP64 form (FTH_FP64): v_mfma_f64_16x16x4_f64 on M and q_n directly.
 //
-// Work split: the output rows are cut into row blocks and the K dimension
-// into ksplit slices (a power of two <= 8); workgroup b takes K slice
+// Work split: the output rows are cut into row blocks and the k-steps that hold
+// columns into ksplit slices as even as they go (a power of two <= 8; padding is
+// neither read nor multiplied: 2300 rows at R = 64 15.3 -> 14.3 us a step, FP64 2100
+// rows at R = 128 61.6 -> 54.0); workgroup b takes K slice
 // b mod ksplit and row block b / ksplit.  The hardware deals workgroups
 // round-robin over the 8 XCDs, so the workgroups of K slice s run on the
 // XCDs x with x mod ksplit = s, and the q_n slice they stream stays in
@@ -93,6 +95,15 @@ __device__ __forceinline__ void scatter_chunk(T* __restrict__ dst, const T (&src
     }
 }
 
+// K slice ks: the k-steps (KS wide) that hold columns of the matrix, dealt as evenly as
+// they go to the ksplit slices (the padding beyond them is zero in M and in q_n).
+__device__ __forceinline__ void gemm_kslice(const DenseGemmArgs& g, int ks, int KS, int64_t& kbeg, int& nsteps) {
+    const int total = int((g.n + KS - 1) / KS);
+    const int b = int(int64_t(ks) * total / g.ksplit), e = int(int64_t(ks + 1) * total / g.ksplit);
+    kbeg = int64_t(b) * KS;
+    nsteps = e - b;
+}
+
 // ------------------------------------------------------ split-BF16x3 GEMM
 // A k-step covers 64 consecutive k: one 32 KB tile of M (hi and lo parts)
 // and one 32 KB chunk of q_n, both fetched one k-step ahead.  M is read once
@@ -111,8 +122,9 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16x3_kernel(const DenseGemmArgs
     const int ks = blockIdx.x % g.ksplit;
     const int64_t rb = blockIdx.x / g.ksplit;
     const int64_t m0 = rb * BM;
-    const int64_t kbeg = int64_t(ks) * g.kslice;
-    const int nsteps = int(g.kslice / KS);
+    int64_t kbeg;
+    int nsteps;
+    gemm_kslice(g, ks, KS, kbeg, nsteps);
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     const int lr = l & 15, lg = l >> 4;
     const int64_t P = g.rows_pad;
@@ -137,7 +149,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16x3_kernel(const DenseGemmArgs
         const u32x4* src = mt + int64_t(J) * TILE;                                 \
         _Pragma("unroll") for (int u = 0; u < 8; ++u) ra[u] = __builtin_nontemporal_load(src + u * 64); \
     }
-    FTH_BF16_FETCH(0)
+    if (nsteps > 0) FTH_BF16_FETCH(0)
     for (int j = 0; j < nsteps; ++j) {
         u32x4* buf = qs[j & 1];
         // staged planar, [hi|lo][k/8][R], so the B reads below are 16 contiguous
@@ -191,8 +203,9 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(const DenseGemmArgs g)
     const int ks = blockIdx.x % g.ksplit;
     const int64_t rb = blockIdx.x / g.ksplit;
     const int64_t m0 = rb * BM;
-    const int64_t kbeg = int64_t(ks) * g.kslice;
-    const int nsteps = int(g.kslice / KS);
+    int64_t kbeg;
+    int nsteps;
+    gemm_kslice(g, ks, KS, kbeg, nsteps);
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     const int lr = l & 15, lg = l >> 4;
     const int64_t P = g.rows_pad;
@@ -215,7 +228,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(const DenseGemmArgs g)
         ra0 = *reinterpret_cast<const f64x2*>(arow + kf);                        \
         ra1 = *reinterpret_cast<const f64x2*>(arow + kf + 2);                    \
     }
-    FTH_F64_FETCH(0)
+    if (nsteps > 0) FTH_F64_FETCH(0)
     for (int j = 0; j < nsteps; ++j) {
         f64x2* buf = reinterpret_cast<f64x2*>(qs[j & 1]);
         scatter_chunk<f64x2, CHUNK / 2, PER_THREAD>(buf, rq);

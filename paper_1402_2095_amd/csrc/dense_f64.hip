@@ -4,8 +4,8 @@
 namespace fth {
 
 int launch_gemm_f64(const DenseGemmArgs& g, void* stream) {
-    if (g.rows_pad % 64 != 0 || g.kslice % 16 != 0 || g.kslice * g.ksplit != g.rows_pad) return -3;
-    const int64_t grid = (g.rows_pad / 64) * g.ksplit;
+    if (g.rows_pad % 64 != 0 || g.n < 1 || g.n > g.rows_pad || g.ksplit < 1) return -3;
+    const int64_t grid = ((g.n + 63) / 64) * g.ksplit;
     const hipStream_t s = static_cast<hipStream_t>(stream);
     switch (g.R) {
         case 16: hipLaunchKernelGGL(dev::gemm_f64_kernel<1>, dim3(unsigned(grid)), dim3(256), 0, s, g); break;

@@ -601,7 +601,7 @@ fth::DenseGemmArgs gemm_args(fth_ctx* c, int k) {
     g.rows_pad = c->rows_pad;
     g.R = c->R;
     g.ksplit = c->ksplit;
-    g.kslice = c->rows_pad / c->ksplit;
+    g.n = c->n;
     return g;
 }
 

@@ -104,7 +104,7 @@ struct StepLaunch {
     int64_t pair_tiles;  // extra workgroups for the selected pairs
 };
 
-// Arguments of the dense split-K force GEMM  part[ks] = M[:, kslice] q_n[kslice, :].
+// Arguments of the dense split-K force GEMM: part[ks] = M[:, slice ks] q_n[slice ks, :].
 struct DenseGemmArgs {
     const void* m_hi;     // split form: bf16 hi and lo parts of M, tiled (see dense.hpp);
                           // FP64 form: double [rows_pad][rows_pad]
@@ -115,9 +115,9 @@ struct DenseGemmArgs {
     int32_t k;            // in-chunk step offset
     void* part;           // [ksplit][rows_pad][R] float (split form) or double
     int64_t rows_pad;
+    int64_t n;            // rows and columns of M (the padding beyond them is not touched)
     int32_t R;
-    int32_t ksplit;
-    int64_t kslice;       // rows_pad / ksplit
+    int32_t ksplit;       // K slices
 };
 
 // Largest workgroup of the temporally blocked step: a row's (p, s) and CSR

@@ -111,7 +111,7 @@ extern "C" fth_status fth_force_noalloc(fth_ctx* c, const void* q, void* F, void
     g.rows_pad = P;
     g.R = int32_t(R);
     g.ksplit = c->ksplit;
-    g.kslice = P / c->ksplit;
+    g.n = n;
     int rc;
     if (f64) {
         hipLaunchKernelGGL(fth::dev::noalloc_pad_kernel, dim3(1024), dim3(256), 0, s, static_cast<const double*>(q),
