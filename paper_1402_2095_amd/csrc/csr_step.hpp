@@ -251,11 +251,11 @@ struct CsrKernels {
             return reinterpret_cast<const void*>(&csr_step_kernel<Real, NS, RPT, NT, false, TR>);
         }
     };
-    // The coded and long-row forms are instantiated for 4 and 8 replicas per thread only.
+    // The coded and long-row forms are instantiated for 2, 4 and 8 replicas per thread.
     template <typename Real, int NS, int RPT, bool NT>
     struct Coded {
         static const void* fn() {
-            if constexpr (RPT >= 4)
+            if constexpr (RPT >= 2)
                 return reinterpret_cast<const void*>(&csr_step_kernel<Real, NS, RPT, NT, true, TR>);
             else
                 return nullptr;
@@ -264,7 +264,7 @@ struct CsrKernels {
     template <typename Real, int NS, int RPT, bool NT>
     struct Long {
         static const void* fn() {
-            if constexpr (RPT >= 4)
+            if constexpr (RPT >= 2)
                 return reinterpret_cast<const void*>(&csr_step_kernel<Real, NS, RPT, NT, false, TR, true>);
             else
                 return nullptr;

@@ -578,14 +578,16 @@ fth::StepArgs<Real> step_args(fth_ctx* c) {
     return a;
 }
 
+// Whether the launch shape has the coded and long-row forms: 4 or 8 replicas per
+// thread, or 2 where a row has at least four replicas.
+bool wide_rows(const fth_ctx* c) { return c->rpt >= 4 || (c->rpt == 2 && c->R >= 4); }
+
 // Plain CSR rows longer than 16 entries take the long-row gather batches.
-bool long_rows(const fth_ctx* c) {
-    return !c->dense() && !(c->coded && c->rpt >= 4) && c->rpt >= 4 && c->max_row_nnz > 16;
-}
+bool long_rows(const fth_ctx* c) { return !c->dense() && !c->coded && wide_rows(c) && c->max_row_nnz > 16; }
 
 fth::StepLaunch step_launch(fth_ctx* c) {
     const int per_block = c->block / (c->R / c->rpt);
-    return fth::StepLaunch{c->ns, c->rpt, c->nt, c->coded && c->rpt >= 4, long_rows(c), c->block,
+    return fth::StepLaunch{c->ns, c->rpt, c->nt, c->coded && wide_rows(c), long_rows(c), c->block,
                            (c->npairs + per_block - 1) / per_block};
 }
 
@@ -893,7 +895,7 @@ fth_status build_graph(fth_ctx* c, int K) {
 
 // ------------------------------------------------------------- autotuner
 // Candidate launch shapes of the sparse step: threads per workgroup,
-// replicas per thread, streaming state access.  Each candidate runs a few
+// replicas per thread (4, 8 and for some systems 2), streaming state access.  Each candidate runs a few
 // steps on the live state, which is saved before and restored after, so
 // tuning leaves the trajectory untouched.  The winner is cached per shape
 // key: precision, GLE size, R, n, nnz, half-bandwidth, longest row and
@@ -976,11 +978,16 @@ fth_status autotune(fth_ctx* c) {
     TuneChoice best{c->block, c->rpt, c->nt, 1e30, 0, 0};
     TuneChoice best4 = best;  // best one-step shape with 4 replicas per thread (tail of blocked chunks)
     const int blocks[3] = {64, 128, 256};
-    const int rpts[2] = {4, 8};
+    // 2 replicas per thread: in FP64, where 4 hold twice the registers (Laplacian 64^3, R = 8:
+    // 44.5 -> 41.2 us a step), and in FP32 systems that leave SIMDs without a wave at 4 (M1
+    // lattice 14^3, R = 16, 172 waves: 12.2 -> 10.5; at 843 waves it measured the same)
+    const bool few_waves = c->n * c->R < int64_t(1024) * 256;
+    const int rpts[3] = {4, 8, 2};
     for (int b : blocks)
         for (int rp : rpts)
             for (int ntv = 0; ntv < 2; ++ntv) {
                 if (rp > c->R || c->R / rp > 64 || c->R / rp > b) continue;
+                if (rp == 2 && c->prec != FTH_FP64 && !few_waves) continue;
                 c->block = b;
                 c->rpt = rp;
                 c->nt = ntv != 0;
@@ -1569,7 +1576,7 @@ fth_status fth_kernel_name(const fth_ctx* c, char* name, size_t len) {
     else
         std::snprintf(name, len, "csr_step_kernel<%s,NS=%d,RPT=%d,NT=%d,CODED=%d> block=%d%s%s",
                       c->prec == FTH_FP64 ? "double" : "float", c->ns, c->rpt, int(c->nt),
-                      int(c->coded && c->rpt >= 4), c->block, long_rows(c) ? " (long-row batches)" : "",
+                      int(c->coded && wide_rows(c)), c->block, long_rows(c) ? " (long-row batches)" : "",
                       c->tuned ? " (autotuned)" : "");
     return FTH_OK;
 }

@@ -192,9 +192,39 @@ __device__ __forceinline__ RowState<Real, NS, RPT> load_row(const StepArgs<Real>
     return st;
 }
 
+// The normals of a row at 2 replicas per lane.  A Philox block serves four replicas, so
+// the two lanes that hold them draw the blocks of one component each and exchange the
+// two words the other needs (DPP): no block is drawn twice, except the last one of an
+// odd number of components.
+template <typename Real, int NS>
+__device__ __forceinline__ void pair_noise(const StepArgs<Real>& a, const StepInfo& si, int64_t i,
+                                           Real (&xi)[NS + 1][2]) {
+    const bool hi = (si.r0 & 2) != 0;
+    const uint32_t grp = uint32_t(si.r0) >> 2;
+    auto other = [](uint32_t v) {  // the value of lane ^ 1
+        return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0xB1, 0xF, 0xF, true));
+    };
+#pragma unroll
+    for (int c = 0; c + 1 <= NS; c += 2) {
+        const Block4 w = philox4x32_10(uint32_t(i), uint32_t(si.n), ((uint32_t(c) + (hi ? 1u : 0u)) << 16) | grp, a.stream,
+                                       a.key0, a.key1);
+        const uint32_t ra = other(hi ? w.w[0] : w.w[2]), rb = other(hi ? w.w[1] : w.w[3]);
+        box_muller(hi ? ra : w.w[0], hi ? rb : w.w[1], xi[c][0], xi[c][1]);
+        box_muller(hi ? w.w[2] : ra, hi ? w.w[3] : rb, xi[c + 1][0], xi[c + 1][1]);
+    }
+    if constexpr ((NS & 1) == 0)
+        normals<Real, 2>(a.key0, a.key1, a.stream, uint32_t(i), uint32_t(si.n), uint32_t(NS), uint32_t(si.r0), xi[NS]);
+}
+
 template <typename Real, int NS, int RPT>
 __device__ __forceinline__ void row_noise(const StepArgs<Real>& a, const StepInfo& si, int64_t i,
                                           Real (&xi)[NS + 1][RPT]) {
+    if constexpr (RPT == 2) {
+        if (a.R >= 4) {  // both lanes of a group of four replicas belong to the row
+            pair_noise<Real, NS>(a, si, i, xi);
+            return;
+        }
+    }
 #pragma unroll
     for (int c = 0; c <= NS; ++c)
         normals<Real, RPT>(a.key0, a.key1, a.stream, uint32_t(i), uint32_t(si.n), uint32_t(c), uint32_t(si.r0),
