@@ -49,6 +49,7 @@ uint64_t hash_words(const void* p, size_t bytes, uint64_t seed) {
 constexpr int kDefaultGraphSteps = 64;
 constexpr int kTbMaxSteps = 5;   // longest temporally blocked launch (snapshot depth)
 constexpr int64_t kReadChunk = 32768;  // estimates per readout chunk (16 bytes each; two chunks are kept pinned)
+constexpr size_t kDenseStage = size_t(64) << 20;  // bytes of a dense M on the device while it is laid out
 constexpr int64_t kTbMaxW = 16;  // widest half-bandwidth blocked
 
 bool is_pow2(int64_t x) { return x > 0 && (x & (x - 1)) == 0; }
@@ -324,85 +325,83 @@ int dense_rows_cols(int64_t n, int R, int prec) {
     return ct;
 }
 
-// Dense M padded to rows_pad x rows_pad with zeros: bf16 hi/lo split on the
-// device for the split form, FP64 as is.
-fth_status upload_dense(fth_ctx* c, const std::vector<double>& M) {
+// Copies the dense M as given to the device, kDenseStage bytes of rows at a time, and
+// calls lay(staged rows, first row, rows given, rows to write) for each part, whose
+// launch converts and pads it; `rows` are written in all.  (A padded copy row by row
+// from pageable memory took 7 ms of a 900-row request's admission.)
+template <typename Lay>
+fth_status stage_dense(fth_ctx* c, int64_t rows, Lay&& lay) {
+    const int64_t n = c->n;
+    const size_t row = size_t(n) * (c->m_src_f64 ? sizeof(double) : sizeof(float));
+    const int64_t part = std::max<int64_t>(int64_t(kDenseStage / row) / 128, 1) * 128;  // whole row blocks
+    ctx_scratch scratch(c);
+    void* buf = scratch.get(row * size_t(std::min(part, n)));
+    if (!buf) return fail(FTH_ENOMEM, "scratch allocation for the dense matrix failed");
+    for (int64_t r0 = 0; r0 < n; r0 += part) {
+        const int64_t given = std::min(part, n - r0);
+        HIP_OK(hipMemcpy(buf, static_cast<const char*>(c->m_src) + size_t(r0) * row, size_t(given) * row,
+                         hipMemcpyHostToDevice));
+        if (lay(buf, r0, given, r0 + part >= n ? rows - r0 : given) != 0)
+            return fail(FTH_EDEVICE, "dense layout launch failed");
+        HIP_OK(hipStreamSynchronize(c->stream));  // the buffer is filled again
+    }
+    return FTH_OK;
+}
+
+// Dense M padded to rows_pad x rows_pad with zeros: bf16 hi/lo split for the split
+// form, FP64 as is.
+fth_status upload_dense(fth_ctx* c) {
     const int64_t n = c->n;
     c->rows_pad = dense_rows_pad(n);
     const int64_t P = c->rows_pad;
     c->ksplit = dense_ksplit(P, c->prec);
     const size_t cnt = size_t(P) * size_t(P);
-    if (c->prec == FTH_FP64) {
-        HIP_OK(c->dalloc(&c->d_m_hi, cnt * sizeof(double)));
-        HIP_OK(hipMemset(c->d_m_hi, 0, cnt * sizeof(double)));
-        HIP_OK(hipMemcpy2D(c->d_m_hi, size_t(P) * 8, M.data(), size_t(n) * 8, size_t(n) * 8, size_t(n),
-                           hipMemcpyHostToDevice));
-        return FTH_OK;
-    }
-    if (c->prec != FTH_FP32_BF16X3)
+    if (c->prec != FTH_FP64 && c->prec != FTH_FP32_BF16X3)
         return fail(FTH_EUNSUPPORTED,
                     "dense systems beyond one workgroup use FTH_FP32_BF16X3 or FTH_FP64 (FTH_FP32 needs replicas <= 8)");
-    ctx_scratch scratch(c);
-    float* tmp = static_cast<float*>(scratch.get(cnt * sizeof(float)));
-    if (!tmp) return fail(FTH_ENOMEM, "scratch allocation for the bf16 split failed");
-    HIP_OK(hipMemset(tmp, 0, cnt * sizeof(float)));
-    {
-        std::vector<float> mf(size_t(n) * size_t(n));
-        for (size_t k = 0; k < mf.size(); ++k) mf[k] = float(M[k]);
-        HIP_OK(hipMemcpy2D(tmp, size_t(P) * 4, mf.data(), size_t(n) * 4, size_t(n) * 4, size_t(n),
-                           hipMemcpyHostToDevice));
+    if (c->prec == FTH_FP64) {
+        HIP_OK(c->dalloc(&c->d_m_hi, cnt * sizeof(double)));
+        return stage_dense(c, P, [&](const void* m, int64_t r0, int64_t given, int64_t rows) {
+            return fth::launch_pad_dense(m, c->m_src_f64, given, n, static_cast<double*>(c->d_m_hi) + r0 * P, true, rows,
+                                         P, c->stream);
+        });
     }
     HIP_OK(c->dalloc(&c->d_m_hi, cnt * 2 * sizeof(uint16_t)));  // hi and lo parts, tiled
-    if (fth::launch_split_bf16_tiled(tmp, c->d_m_hi, P, c->stream) != 0)
-        return fail(FTH_EDEVICE, "bf16 split launch failed");
-    HIP_OK(hipStreamSynchronize(c->stream));
-    return FTH_OK;
+    return stage_dense(c, P, [&](const void* m, int64_t r0, int64_t given, int64_t rows) {
+        return fth::launch_split_bf16_tiled(m, c->m_src_f64, given, n, static_cast<char*>(c->d_m_hi) + r0 * P * 4, rows, P,
+                                            c->stream);
+    });
 }
 
 // Small dense systems: M [n][n] in the state precision for the persistent kernel,
 // column-major, so that the threads of consecutive rows read consecutive words
 // (M is only symmetric to the validation tolerance, so the copy is a transpose).
-fth_status upload_small(fth_ctx* c, const std::vector<double>& M) {
-    const size_t cnt = M.size();
+template <typename Real>
+fth_status upload_small(fth_ctx* c) {
     const size_t n = size_t(c->n);
-    if (c->prec == FTH_FP64) {
-        std::vector<double> mt(cnt);
-        for (size_t i = 0; i < n; ++i)
-            for (size_t j = 0; j < n; ++j) mt[j * n + i] = M[i * n + j];
-        HIP_OK(c->dalloc(&c->d_msmall, cnt * sizeof(double)));
-        HIP_OK(hipMemcpy(c->d_msmall, mt.data(), cnt * sizeof(double), hipMemcpyHostToDevice));
-    } else {
-        std::vector<float> mf(cnt);
-        for (size_t i = 0; i < n; ++i)
-            for (size_t j = 0; j < n; ++j) mf[j * n + i] = float(M[i * n + j]);
-        HIP_OK(c->dalloc(&c->d_msmall, cnt * sizeof(float)));
-        HIP_OK(hipMemcpy(c->d_msmall, mf.data(), cnt * sizeof(float), hipMemcpyHostToDevice));
-    }
+    std::vector<Real> mt(n * n);
+    for (size_t i = 0; i < n; ++i)
+        for (size_t j = 0; j < n; ++j)
+            mt[j * n + i] = c->m_src_f64 ? Real(static_cast<const double*>(c->m_src)[i * n + j])
+                                         : Real(static_cast<const float*>(c->m_src)[i * n + j]);
+    HIP_OK(c->dalloc(&c->d_msmall, mt.size() * sizeof(Real)));
+    HIP_OK(hipMemcpy(c->d_msmall, mt.data(), mt.size() * sizeof(Real), hipMemcpyHostToDevice));
     return FTH_OK;
 }
 
 // Dense M for the few-replica force (R < 16): row-major in the state precision
 // (FP32 for both FP32 forms), ld = n rounded up to 4, zero columns past n.
-fth_status upload_gemv(fth_ctx* c, const std::vector<double>& M) {
+fth_status upload_gemv(fth_ctx* c) {
     const int64_t n = c->n, ld = (n + 3) / 4 * 4;
     c->rows_pad = ld;
     c->ksplit = 1;
     c->gemv = true;
-    const size_t cnt = size_t(n) * size_t(ld);
-    if (c->prec == FTH_FP64) {
-        std::vector<double> m(cnt, 0.0);
-        for (int64_t i = 0; i < n; ++i)
-            for (int64_t j = 0; j < n; ++j) m[size_t(i * ld + j)] = M[size_t(i * n + j)];
-        HIP_OK(c->dalloc(&c->d_m_hi, cnt * sizeof(double)));
-        HIP_OK(hipMemcpy(c->d_m_hi, m.data(), cnt * sizeof(double), hipMemcpyHostToDevice));
-    } else {
-        std::vector<float> m(cnt, 0.0f);
-        for (int64_t i = 0; i < n; ++i)
-            for (int64_t j = 0; j < n; ++j) m[size_t(i * ld + j)] = float(M[size_t(i * n + j)]);
-        HIP_OK(c->dalloc(&c->d_m_hi, cnt * sizeof(float)));
-        HIP_OK(hipMemcpy(c->d_m_hi, m.data(), cnt * sizeof(float), hipMemcpyHostToDevice));
-    }
-    return FTH_OK;
+    const bool f64 = c->prec == FTH_FP64;
+    HIP_OK(c->dalloc(&c->d_m_hi, size_t(n) * size_t(ld) * c->real_bytes()));
+    return stage_dense(c, n, [&](const void* m, int64_t r0, int64_t given, int64_t rows) {
+        return fth::launch_pad_dense(m, c->m_src_f64, given, n, static_cast<char*>(c->d_m_hi) + r0 * ld * (f64 ? 8 : 4),
+                                     f64, rows, ld, c->stream);
+    });
 }
 
 std::vector<double> dense_to_double(const fth_matrix* M) {
@@ -442,16 +441,17 @@ fth_status ensure_state(fth_ctx* c, int32_t R) {
             c->small_lds = lds_base + (c->small_m_in_lds ? size_t(c->n) * size_t(c->n) * rb : 0);
             c->small_quad = c->n <= fth::kSmallQuadRows &&
                             fth::small_quad_lds(c->n, R, c->ns, c->prec == FTH_FP64) <= kSmallMaxLds;
-            st2 = upload_small(c, c->m_host);
+            st2 = c->prec == FTH_FP64 ? upload_small<double>(c) : upload_small<float>(c);
         } else if (R == 1 || R == 2 || R == 4 || R == 8) {
-            st2 = upload_gemv(c, c->m_host);
+            st2 = upload_gemv(c);
         } else {
             if (R != 16 && R != 32 && R != 64 && R != 128)
                 return fail(FTH_EUNSUPPORTED, "dense systems of this size need R in {1, 2, 4, 8, 16, 32, 64, 128} (got %d)",
                             R);
-            st2 = upload_dense(c, c->m_host);
+            st2 = upload_dense(c);
         }
         if (st2 != FTH_OK) return st2;
+        c->m_src = nullptr;
         c->m_host.clear();
         c->m_host.shrink_to_fit();
         c->m_uploaded = true;
@@ -1238,16 +1238,10 @@ fth_status fth_create(const fth_matrix* M_in, const fth_gle* gle_in, double dt, 
 
     // matrix
     if (c->dense()) {
-        c->m_host = dense_to_double(M);
-        if (M->n > kSmallMaxNR && opt.replicas != 0) {  // no single-workgroup path for any R
-            const int32_t R0 = opt.replicas;
-            st = (R0 == 1 || R0 == 2 || R0 == 4 || R0 == 8) ? upload_gemv(c.get(), c->m_host)
-                                                             : upload_dense(c.get(), c->m_host);
-            if (st != FTH_OK) return st;
-            c->m_host.clear();
-            c->m_host.shrink_to_fit();
-            c->m_uploaded = true;
-        }
+        // with R given, the matrix is laid out below, from the caller's array
+        if (opt.replicas == 0) c->m_host = dense_to_double(M);
+        c->m_src = opt.replicas == 0 ? static_cast<const void*>(c->m_host.data()) : M->dense;
+        c->m_src_f64 = opt.replicas == 0 || M->value_is_f64 != 0;
     } else {
         int64_t w = 0, maxnz = 0;
         for (int64_t i = 0; i < M->n; ++i) {

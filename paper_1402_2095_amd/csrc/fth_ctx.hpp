@@ -46,7 +46,10 @@ struct fth_ctx {
     int small_m_in_lds = 0;
     bool small_quad = false;  // small system of at most kSmallQuadRows rows: M in registers, estimates from d_traj
     void* d_traj[3] = {nullptr, nullptr, nullptr};  // q, p, M q of a chunk of steps, [kSmallQuadSteps][n][R]
-    std::vector<double> m_host;  // dense M kept until R fixes the path (n <= 4096)
+    // dense M [n][n] until R fixes the path: the caller's array during create, else the copy in m_host
+    const void* m_src = nullptr;
+    bool m_src_f64 = false;
+    std::vector<double> m_host;
     bool m_uploaded = false;
     void* d_q[2] = {nullptr, nullptr};
     void* d_ps[2] = {nullptr, nullptr};  // p then s_1..s_ns, ping-pong by step parity,

@@ -228,8 +228,14 @@ int launch_gemv_force(const Real* M, int64_t ld, int64_t N, int R, const Real* q
 // workgroup).  At 8 FP32 replicas q_n costs as many bytes from L2 as 8 rows of M, so
 // sixteen rows share it.
 constexpr int gemv_rows(bool f64, int R) { return !f64 && R == 8 ? 16 : 8; }
-// M [P][P] FP32 -> bf16 hi/lo parts in the split GEMM's tiled layout (4 P^2 bytes at mt).
-int launch_split_bf16_tiled(const float* m, void* mt, int64_t P, void* stream);
+// `given` rows of M (n columns; float, or double rounded to float) -> bf16 hi/lo parts of
+// `rows` rows (a multiple of 128) in the split GEMM's tiled layout, zero padded; mt is the
+// first row's row block.
+int launch_split_bf16_tiled(const void* m, bool m_f64, int64_t given, int64_t n, void* mt, int64_t rows, int64_t P,
+                            void* stream);
+// `given` rows of M (n columns; float or double) -> [rows][ld] in the state precision, zero padded.
+int launch_pad_dense(const void* m, bool m_f64, int64_t given, int64_t n, void* out, bool out_f64, int64_t rows,
+                     int64_t ld, void* stream);
 int launch_qt_from_q(const float* q, uint16_t* qt, int64_t N, int64_t rows_pad, int32_t R, void* stream);
 int launch_advance(int64_t* step_base, int64_t k, void* stream);
 // Trace estimators: sum the per-tile partials of K steps (fixed order), fold
