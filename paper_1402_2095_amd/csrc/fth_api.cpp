@@ -88,15 +88,17 @@ fth_status check_csr(const fth_matrix* M) {
         if (!diag) return fail(FTH_EINVAL, "missing diagonal entry in row %lld", (long long)i);
     }
     const double tol = (M->value_is_f64 ? 1e-12 : 1e-6) * vmax;
+    // Rows are visited in order and columns increase, so the entries of row j meet their
+    // mirror images (i, j) in order: next[j] is the first one not met yet.  (A search per
+    // entry took 1 ms of a 40000-row request's admission.)
+    std::vector<int64_t> next(M->row_ptr, M->row_ptr + n);
     for (int64_t i = 0; i < n; ++i) {
         for (int64_t k = M->row_ptr[i]; k < M->row_ptr[i + 1]; ++k) {
             const int32_t j = M->col[k];
-            if (j == i) continue;
-            const int32_t* b = M->col + M->row_ptr[j];
-            const int32_t* e = M->col + M->row_ptr[j + 1];
-            const int32_t* f = std::lower_bound(b, e, int32_t(i));
-            if (f == e || *f != i) return fail(FTH_EINVAL, "CSR pattern not symmetric at (%lld, %d)", (long long)i, j);
-            if (std::fabs(val(f - M->col) - val(k)) > tol)
+            const int64_t f = next[size_t(j)]++;
+            if (f >= M->row_ptr[j + 1] || M->col[f] != i)
+                return fail(FTH_EINVAL, "CSR pattern not symmetric at (%lld, %d)", (long long)i, j);
+            if (std::fabs(val(f) - val(k)) > tol)
                 return fail(FTH_EINVAL, "CSR values not symmetric at (%lld, %d)", (long long)i, j);
         }
     }

@@ -88,6 +88,66 @@ struct Group {
     }
 };
 
+// Device memory of finished requests, kept for the next ones: a request's dozen
+// hipMalloc and hipFree calls (each free waits for the device) took up to 4 ms of its
+// life.  A context has waited for its stream before it gives a block back, so a block
+// may go to any other stream.  Bounded by kPoolBytes, given back when an allocation
+// fails and when the server goes; one pool per server, used by the server's caller only.
+constexpr size_t kPoolBytes = size_t(1) << 30;
+
+struct DevicePool {
+    fth_allocator hook{};
+    std::multimap<size_t, void*> idle;  // by size
+    std::map<void*, size_t> size;       // of every block
+    size_t idle_bytes = 0;
+
+    DevicePool() {
+        hook.alloc = [](size_t bytes, void* user) { return static_cast<DevicePool*>(user)->get(bytes); };
+        hook.release = [](void* p, void* user) { static_cast<DevicePool*>(user)->put(p); };
+        hook.user = this;
+    }
+    DevicePool(const DevicePool&) = delete;
+    DevicePool& operator=(const DevicePool&) = delete;
+    ~DevicePool() { drop(); }
+
+    void* get(size_t bytes) {
+        const size_t want = std::max<size_t>((bytes + 255) / 256 * 256, 256);
+        auto it = idle.lower_bound(want);
+        if (it != idle.end() && it->first <= want + want / 2) {  // no block more than half too large
+            void* p = it->second;
+            idle_bytes -= it->first;
+            idle.erase(it);
+            return p;
+        }
+        void* p = nullptr;
+        if (hipMalloc(&p, want) != hipSuccess) {
+            (void)hipGetLastError();
+            drop();
+            if (hipMalloc(&p, want) != hipSuccess) return nullptr;
+        }
+        size[p] = want;
+        return p;
+    }
+    void put(void* p) {
+        const size_t b = size[p];
+        if (idle_bytes + b <= kPoolBytes) {
+            idle.emplace(b, p);
+            idle_bytes += b;
+        } else {
+            size.erase(p);
+            (void)hipFree(p);
+        }
+    }
+    void drop() {
+        for (auto& kv : idle) {
+            size.erase(kv.second);
+            (void)hipFree(kv.second);
+        }
+        idle.clear();
+        idle_bytes = 0;
+    }
+};
+
 bool packable(const SrvRequest& r) {
     return r.M.format == FTH_CSR && r.opt.precision == FTH_FP32 && r.opt.replicas % 4 == 0 && r.opt.replicas >= 4 &&
            r.opt.replicas <= 256 && r.gle.ns <= fth::kNsMax;
@@ -97,6 +157,7 @@ bool packable(const SrvRequest& r) {
 
 struct fth_server {
     fth_server_options opt{};
+    DevicePool pool;  // outlives every context (destroyed in the destructor's body)
     std::chrono::steady_clock::time_point t0;
     int device = 0;
     uint64_t next_id = 1;
@@ -276,6 +337,7 @@ void finish(fth_server* s, SrvRequest* r, int32_t state, fth_status st) {
 
 fth_status admit(fth_server* s, SrvRequest* r) {
     fth_ctx* c = nullptr;
+    r->opt.allocator = &s->pool.hook;
     fth_status st = fth_create(&r->M, &r->gle, r->dt, r->pairs.empty() ? nullptr : r->pairs.data(),
                                int64_t(r->pairs.size() / 2), &r->opt, &c);
     if (st != FTH_OK) return st;
