@@ -442,7 +442,7 @@ fth_status ensure_state(fth_ctx* c, int32_t R) {
             c->small_m_in_lds = lds_base + size_t(c->n) * size_t(c->n) * rb <= kSmallMaxLds;
             c->small_lds = lds_base + (c->small_m_in_lds ? size_t(c->n) * size_t(c->n) * rb : 0);
             c->small_quad = c->n <= fth::kSmallQuadRows &&
-                            fth::small_quad_lds(c->n, R, c->ns, c->prec == FTH_FP64) <= kSmallMaxLds;
+                            fth::small_quad_lds(c->n, c->ns, c->prec == FTH_FP64) <= kSmallMaxLds;
             st2 = c->prec == FTH_FP64 ? upload_small<double>(c) : upload_small<float>(c);
         } else if (R == 1 || R == 2 || R == 4 || R == 8) {
             st2 = upload_gemv(c);
@@ -708,23 +708,22 @@ fth_status enqueue_trace_fold(fth_ctx* c, int K, int64_t shift) {
 }
 
 template <typename Real>
-int launch_quad(fth_ctx* c, int K) {
+int launch_quad(fth_ctx* c, int64_t n0, int K) {
     const fth::SmallTraj<Real> tj{static_cast<Real*>(c->d_traj[0]), static_cast<Real*>(c->d_traj[1]),
                                   static_cast<Real*>(c->d_traj[2])};
-    return fth::launch_small_quad<Real>(step_args<Real>(c), tj, K, c->stream);
+    return fth::launch_small_quad<Real>(step_args<Real>(c), tj, n0, K, c->stream);
 }
 
 fth_status enqueue_small_quad(fth_ctx* c, int64_t nsteps) {
     for (int64_t done = 0; done < nsteps;) {
         const int K = int(std::min<int64_t>(nsteps - done, fth::kSmallQuadSteps));
-        const int rc = c->prec == FTH_FP64 ? launch_quad<double>(c, K) : launch_quad<float>(c, K);
+        const int rc = c->prec == FTH_FP64 ? launch_quad<double>(c, c->step + done, K) : launch_quad<float>(c, c->step + done, K);
         if (rc == -2) return fail(FTH_EUNSUPPORTED, "no kernel instantiated for ns=%d", c->ns);
         if (rc != 0) return fail(FTH_EDEVICE, "small-system kernel launch failed (%d)", rc);
         if (c->opt.acc_trace) {
-            fth_status st = enqueue_trace_fold(c, K, 0);
+            fth_status st = enqueue_trace_fold(c, K, -int64_t(K));  // the kernel has advanced the counter
             if (st != FTH_OK) return st;
         }
-        if (fth::launch_advance(c->d_step, K, c->stream) != 0) return fail(FTH_EDEVICE, "advance launch failed");
         done += K;
     }
     return FTH_OK;
@@ -1546,8 +1545,8 @@ int32_t fth_launches_per_step(const fth_ctx* c) { return c ? (c->mfma() && !c->g
 fth_status fth_kernel_name(const fth_ctx* c, char* name, size_t len) {
     if (!c || !name || len == 0) return fail(FTH_EINVAL, "invalid arguments");
     if (c->small_quad)
-        std::snprintf(name, len, "small_dense_kernel_quad<%s,NS=%d,RR=%d> (M in registers)",
-                      c->prec == FTH_FP64 ? "double" : "float", c->ns, std::min(c->R, 4));
+        std::snprintf(name, len, "small_dense_kernel_quad<%s,NS=%d> (M in registers)",
+                      c->prec == FTH_FP64 ? "double" : "float", c->ns);
     else if (c->small)
         std::snprintf(name, len, "small_dense_kernel<%s,NS=%d,RPT=%d> (persistent, M in %s)",
                       c->prec == FTH_FP64 ? "double" : "float", c->ns, c->rpt, c->small_m_in_lds ? "LDS" : "global");

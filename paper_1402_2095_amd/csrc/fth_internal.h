@@ -290,14 +290,13 @@ struct SmallTraj {
 constexpr int kSmallQuadRows = 128;
 // Steps per launch: bounds the trajectory buffer at 8 MB per kind (n R <= 4096 in FP64).
 constexpr int kSmallQuadSteps = 256;
-constexpr size_t small_quad_lds(int64_t n, int R, int ns, bool f64) {
-    const size_t rr = R < 4 ? size_t(R) : 4, d = size_t(ns) + 1;
-    const size_t rows = size_t(n * 4 + 63) / 64 * 16, cols = n <= 64 ? 64 : 128;
-    return (2 * cols * rr + 4 * d * rows * rr + 2 * d * d) * (f64 ? 8 : 4);
+constexpr size_t small_quad_lds(int64_t n, int ns, bool f64) {
+    const size_t d = size_t(ns) + 1, rows = size_t(n * 4 + 63) / 64 * 16, cols = n <= 64 ? 64 : 128;
+    return (2 * cols + 4 * d * rows + 2 * d * d) * (f64 ? 8 : 4);
 }
-// K <= kSmallQuadSteps steps and their estimates; the step counter is left as it is.
+// Steps n0 .. n0 + K - 1 (K <= kSmallQuadSteps), the step counter and the estimates.
 template <typename Real>
-int launch_small_quad(const StepArgs<Real>& a, const SmallTraj<Real>& tj, int K, void* stream);
+int launch_small_quad(const StepArgs<Real>& a, const SmallTraj<Real>& tj, int64_t n0, int K, void* stream);
 
 // Host FP64 linear algebra (fth_linalg.cpp).
 namespace la {

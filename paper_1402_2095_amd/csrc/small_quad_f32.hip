@@ -3,7 +3,7 @@
 
 namespace fth {
 template <>
-int launch_small_quad<float>(const StepArgs<float>& a, const SmallTraj<float>& tj, int K, void* stream) {
-    return launch_small_quad_impl<float>(a, tj, K, stream);
+int launch_small_quad<float>(const StepArgs<float>& a, const SmallTraj<float>& tj, int64_t n0, int K, void* stream) {
+    return launch_small_quad_impl<float>(a, tj, n0, K, stream);
 }
 }  // namespace fth

@@ -3,7 +3,7 @@
 
 namespace fth {
 template <>
-int launch_small_quad<double>(const StepArgs<double>& a, const SmallTraj<double>& tj, int K, void* stream) {
-    return launch_small_quad_impl<double>(a, tj, K, stream);
+int launch_small_quad<double>(const StepArgs<double>& a, const SmallTraj<double>& tj, int64_t n0, int K, void* stream) {
+    return launch_small_quad_impl<double>(a, tj, n0, K, stream);
 }
 }  // namespace fth
