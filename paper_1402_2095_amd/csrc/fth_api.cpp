@@ -490,6 +490,11 @@ fth_status ensure_state(fth_ctx* c, int32_t R) {
     if (c->mfma() && !c->gemv) {
         c->rows_ct = dense_rows_cols(c->n, R, c->prec);
         if (c->rows_ct == 0) {
+            // The FP64 epilogue is a long chain on few waves: two replicas per thread (two lanes
+            // share a noise block) halve it.  4000 rows R = 32 33.2 -> 32.2 us a step, 2100 rows
+            // R = 32 22.0 -> 20.5, 4990 rows R = 128 149.3 -> 147.0; in FP32 it measured 1 % better
+            // below 1024 waves and up to 5 % worse above, so four stay.
+            if (c->prec == FTH_FP64 && c->n * R < (int64_t(1) << 20)) c->rpt = 2;
             const size_t pb = size_t(c->ksplit) * size_t(c->rows_pad) * size_t(R) * rb;
             HIP_OK(c->dalloc(&c->d_part, pb));
             HIP_OK(hipMemsetAsync(c->d_part, 0, pb, c->stream));
