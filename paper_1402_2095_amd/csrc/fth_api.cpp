@@ -289,8 +289,8 @@ fth_status upload_TS(fth_ctx* c) {
     return FTH_OK;
 }
 
-// Padded size of a dense M: a multiple of 256, and of 512 from 2048 on, where
-// the split-K GEMM cuts K into 8 slices that must each be whole 64-wide k-steps.
+// Padded size of a dense M: a multiple of 256, and of 512 from 2048 on (the GEMM
+// multiplies the k-steps and row blocks that hold the matrix; the rest is zero).
 int64_t dense_rows_pad(int64_t n) {
     const int64_t p = (n + 255) / 256 * 256;
     return p >= 2048 ? (n + 511) / 512 * 512 : p;
@@ -1143,6 +1143,8 @@ size_t fth_footprint_bytes(const fth_matrix* M, int32_t ns, int32_t R, int64_t n
         if (!rows) bytes += ks * P * size_t(R) * rb;                           // split-K partials
         if (precision == FTH_FP32_BF16X3) bytes += P * size_t(R) * (rows ? 8 : 4);  // bf16 q split(s)
     }
+    if (M->format == FTH_DENSE && n <= size_t(fth::kSmallQuadRows) && R > 0 && int64_t(n) * R <= kSmallMaxNR)
+        bytes += size_t(fth::kSmallQuadSteps) * n * size_t(R) * rb;            // trajectory of a chunk of steps
     const size_t nout = size_t(npairs) + (acc_diag ? n : 0);
     bytes += nout * 24 + size_t(npairs) * 8;
     bytes += 2 * size_t(ns + 1) * size_t(ns + 1) * rb + 64;
