@@ -80,28 +80,65 @@ __device__ __forceinline__ void csr_row(const StepArgs<Real>& a, const StepInfo&
 #pragma unroll
             for (int m = 0; m < RPT; ++m) acc[m] = fmaR(vj[u], qj[u].v[m], acc[m]);
         }
-    for (int64_t base = kb + G; base < ke; base += GL) {  // rows longer than one batch
-        V ql[GL];
-        Real vl[GL];
-        int32_t cl[GL];
+    if constexpr (LONG) {
+        // Entries past the row repeat its last one and their products are dropped, so the
+        // loads of a batch need no masks: M1 14^3 R = 16 10.4 -> 9.3 us a step, 16^3 R = 32
+        // 12.7 -> 11.7, 24^3 R = 32 19.0 -> 18.7.
+        for (int64_t base = kb + G; base < ke; base += GL) {
+            const int64_t left = ke - base;
+            const int cnt = int(left < GL ? left : GL);
+            const Real* vp = a.val + base;
+            const int32_t* cp = a.col + base;
+            V ql[GL];
+            Real vl[GL];
+            int32_t cl[GL];
 #pragma unroll
-        for (int u = 0; u < GL; ++u) {
-            vl[u] = Real(0);
-            cl[u] = 0;
-            if (base + u < ke) {
-                vl[u] = a.val[base + u];
-                cl[u] = a.col[base + u];
+            for (int u = 0; u < GL; ++u) {
+                const int v = min(u, cnt - 1);
+                vl[u] = vp[v];
+                cl[u] = cp[v];
+            }
+#pragma unroll
+            for (int u = 0; u < GL; ++u) ql[u] = load_vec<Real, RPT>(qr + int64_t(cl[u]) * R + si.r0);
+            if (__all(cnt == GL)) {
+#pragma unroll
+                for (int u = 0; u < GL; ++u)
+#pragma unroll
+                    for (int m = 0; m < RPT; ++m) acc[m] = fmaR(vl[u], ql[u].v[m], acc[m]);
+            } else {
+#pragma unroll
+                for (int u = 0; u < GL; ++u)
+#pragma unroll
+                    for (int m = 0; m < RPT; ++m) {
+                        const Real t = fmaR(vl[u], ql[u].v[m], acc[m]);
+                        acc[m] = u < cnt ? t : acc[m];
+                    }
             }
         }
-#pragma unroll
-        for (int u = 0; u < GL; ++u)
-            if (base + u < ke) ql[u] = load_vec<Real, RPT>(qr + int64_t(cl[u]) * R + si.r0);
-#pragma unroll
-        for (int u = 0; u < GL; ++u)
-            if (base + u < ke) {
-#pragma unroll
-                for (int m = 0; m < RPT; ++m) acc[m] = fmaR(vl[u], ql[u].v[m], acc[m]);
+    } else {
+        for (int64_t base = kb + G; base < ke; base += GL) {  // rows longer than one batch
+            V ql[GL];
+            Real vl[GL];
+            int32_t cl[GL];
+    #pragma unroll
+            for (int u = 0; u < GL; ++u) {
+                vl[u] = Real(0);
+                cl[u] = 0;
+                if (base + u < ke) {
+                    vl[u] = a.val[base + u];
+                    cl[u] = a.col[base + u];
+                }
             }
+    #pragma unroll
+            for (int u = 0; u < GL; ++u)
+                if (base + u < ke) ql[u] = load_vec<Real, RPT>(qr + int64_t(cl[u]) * R + si.r0);
+    #pragma unroll
+            for (int u = 0; u < GL; ++u)
+                if (base + u < ke) {
+    #pragma unroll
+                    for (int m = 0; m < RPT; ++m) acc[m] = fmaR(vl[u], ql[u].v[m], acc[m]);
+                }
+        }
     }
     (void)finish_row<Real, NS, RPT, NT>(a, si, i, st, acc, xi, qw, trow);
 }
