@@ -96,12 +96,12 @@ __device__ __forceinline__ void scatter_chunk(T* __restrict__ dst, const T (&src
 }
 
 // K slice ks: the k-steps (KS wide) that hold columns of the matrix, dealt as evenly as
-// they go to the ksplit slices (the padding beyond them is zero in M and in q_n).
+// they go to the ksplit slices (the padding beyond them is zero in M and in q_n).  The
+// launchers divide (a 64-bit division here took 4 % of the FP64 GEMM at 16384 rows) and
+// check that every slice has a k-step.
 __device__ __forceinline__ void gemm_kslice(const DenseGemmArgs& g, int ks, int KS, int64_t& kbeg, int& nsteps) {
-    const int total = int((g.n + KS - 1) / KS);
-    const int b = int(int64_t(ks) * total / g.ksplit), e = int(int64_t(ks + 1) * total / g.ksplit);
-    kbeg = int64_t(b) * KS;
-    nsteps = e - b;
+    kbeg = int64_t(ks * g.kq + min(ks, g.krem)) * KS;
+    nsteps = g.kq + (ks < g.krem ? 1 : 0);
 }
 
 // ------------------------------------------------------ split-BF16x3 GEMM
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16x3_kernel(const DenseGemmArgs
         const u32x4* src = mt + int64_t(J) * TILE;                                 \
         _Pragma("unroll") for (int u = 0; u < 8; ++u) ra[u] = __builtin_nontemporal_load(src + u * 64); \
     }
-    if (nsteps > 0) FTH_BF16_FETCH(0)
+    FTH_BF16_FETCH(0)
     for (int j = 0; j < nsteps; ++j) {
         u32x4* buf = qs[j & 1];
         // staged planar, [hi|lo][k/8][R], so the B reads below are 16 contiguous
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(const DenseGemmArgs g)
         ra0 = *reinterpret_cast<const f64x2*>(arow + kf);                        \
         ra1 = *reinterpret_cast<const f64x2*>(arow + kf + 2);                    \
     }
-    if (nsteps > 0) FTH_F64_FETCH(0)
+    FTH_F64_FETCH(0)
     for (int j = 0; j < nsteps; ++j) {
         f64x2* buf = reinterpret_cast<f64x2*>(qs[j & 1]);
         scatter_chunk<f64x2, CHUNK / 2, PER_THREAD>(buf, rq);

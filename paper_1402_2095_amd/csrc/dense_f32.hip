@@ -58,8 +58,11 @@ __global__ void qt_from_q_kernel(const float* __restrict__ q, uint16_t* __restri
 
 }  // namespace dev
 
-int launch_gemm_bf16x3(const DenseGemmArgs& g, void* stream) {
-    if (g.rows_pad % 128 != 0 || g.n < 1 || g.n > g.rows_pad || g.ksplit < 1) return -3;
+int launch_gemm_bf16x3(const DenseGemmArgs& g0, void* stream) {
+    DenseGemmArgs g = g0;
+    if (g.rows_pad % 128 != 0 || g.n > g.rows_pad || g.ksplit < 1 || (g.n + 63) / 64 < g.ksplit) return -3;
+    g.kq = int32_t((g.n + 63) / 64 / g.ksplit);
+    g.krem = int32_t((g.n + 63) / 64 % g.ksplit);
     const int64_t grid = ((g.n + 127) / 128) * g.ksplit;
     const hipStream_t s = static_cast<hipStream_t>(stream);
     switch (g.R) {

@@ -3,8 +3,11 @@
 
 namespace fth {
 
-int launch_gemm_f64(const DenseGemmArgs& g, void* stream) {
-    if (g.rows_pad % 64 != 0 || g.n < 1 || g.n > g.rows_pad || g.ksplit < 1) return -3;
+int launch_gemm_f64(const DenseGemmArgs& g0, void* stream) {
+    DenseGemmArgs g = g0;
+    if (g.rows_pad % 64 != 0 || g.n > g.rows_pad || g.ksplit < 1 || (g.n + 15) / 16 < g.ksplit) return -3;
+    g.kq = int32_t((g.n + 15) / 16 / g.ksplit);
+    g.krem = int32_t((g.n + 15) / 16 % g.ksplit);
     const int64_t grid = ((g.n + 63) / 64) * g.ksplit;
     const hipStream_t s = static_cast<hipStream_t>(stream);
     switch (g.R) {

@@ -140,11 +140,10 @@ __device__ __forceinline__ void rows_estimates(const StepArgs<Real>& a, int k, i
 // Row block and column group of workgroup b: the column groups of a row block go to
 // the same XCD (workgroups are dealt round-robin over the 8), so its rows of M are
 // read into one L2.
-__device__ __forceinline__ bool rows_tile(int64_t b, int cgroups, int64_t N, int64_t& rg, int& cg) {
-    const int64_t hi = b / (8 * cgroups);
-    const int lo = int(b % (8 * cgroups));
-    cg = lo >> 3;
-    rg = hi * 8 + (lo & 7);
+// (cgroups is a power of two.)
+__device__ __forceinline__ bool rows_tile(uint32_t b, int cgroups, int64_t N, int64_t& rg, int& cg) {
+    cg = int(b >> 3) & (cgroups - 1);
+    rg = int64_t(b >> (3 + __builtin_ctz(uint32_t(cgroups)))) * 8 + (b & 7);
     return rg * 16 < N;
 }
 

@@ -118,6 +118,7 @@ struct DenseGemmArgs {
     int64_t n;            // rows and columns of M (the padding beyond them is not touched)
     int32_t R;
     int32_t ksplit;       // K slices
+    int32_t kq, krem;     // (filled by the launchers) k-steps per slice, slices with one more
 };
 
 // Largest workgroup of the temporally blocked step: a row's (p, s) and CSR
