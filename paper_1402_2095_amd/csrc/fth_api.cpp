@@ -693,7 +693,7 @@ fth_status trace_prepare(fth_ctx* c, int K) {
     c->dfree(reinterpret_cast<void*&>(c->d_tsum));
     const size_t pb = sizeof(double) * 3 * size_t(nk) * size_t(nw);
     HIP_OK(c->dalloc(reinterpret_cast<void**>(&c->d_tpart), pb));
-    HIP_OK(hipMemset(c->d_tpart, 0, pb));
+    HIP_OK(hipMemsetAsync(c->d_tpart, 0, pb, c->stream));
     HIP_OK(c->dalloc(reinterpret_cast<void**>(&c->d_tsum), sizeof(double) * 3 * size_t(nk)));
     c->tpart_k = nk;
     c->tpart_w = nw;
@@ -1279,15 +1279,17 @@ fth_status fth_create(const fth_matrix* M_in, const fth_gle* gle_in, double dt, 
     if (npairs > 0) HIP_OK(hipMemcpy(c->d_pairs, pairs, sizeof(int32_t) * size_t(2 * npairs), hipMemcpyHostToDevice));
     const size_t accb = sizeof(double) * size_t(3 * c->n_out());
     HIP_OK(c->dalloc(reinterpret_cast<void**>(&c->d_acc), accb));
-    HIP_OK(hipMemset(c->d_acc, 0, std::max<size_t>(accb, 8)));
+    // (fills go to the context's stream: nothing orders that stream after the null stream)
+    HIP_OK(hipMemsetAsync(c->d_acc, 0, std::max<size_t>(accb, 8), c->stream));
     HIP_OK(c->dalloc(reinterpret_cast<void**>(&c->d_step), sizeof(int64_t)));
-    HIP_OK(hipMemset(c->d_step, 0, sizeof(int64_t)));
+    HIP_OK(hipMemsetAsync(c->d_step, 0, sizeof(int64_t), c->stream));
     HIP_OK(hipHostMalloc(reinterpret_cast<void**>(&c->h_flag), sizeof(int32_t), hipHostMallocDefault));
     *c->h_flag = 0;
     if (opt.replicas != 0) {
         st = ensure_state(c.get(), opt.replicas);
         if (st != FTH_OK) return st;
     }
+    HIP_OK(hipStreamSynchronize(c->stream));  // other streams and copies may follow at once
     *out = c.release();
     return FTH_OK;
 }
@@ -1499,8 +1501,10 @@ fth_status fth_force(fth_ctx* c, const double* q, double* F) {
     const bool split = c->prec == FTH_FP32_BF16X3 && !c->gemv;
     uint16_t* dqt = split ? static_cast<uint16_t*>(alloc(size_t(P * R) * 4)) : nullptr;
     if (!dq || !dpart || !dstep || (split && !dqt)) return fail(FTH_ENOMEM, "scratch allocation failed");
-    HIP_OK(hipMemset(dq, 0, size_t(P * R) * rb));
-    HIP_OK(hipMemset(dstep, 0, sizeof(int64_t)));
+    HIP_OK(hipMemsetAsync(dq, 0, size_t(P * R) * rb, c->stream));
+    HIP_OK(hipMemsetAsync(dstep, 0, sizeof(int64_t), c->stream));
+    if (split) HIP_OK(hipMemsetAsync(dqt, 0, size_t(P * R) * 4, c->stream));
+    HIP_OK(hipStreamSynchronize(c->stream));  // the copies below go over the null stream
     if (c->prec == FTH_FP64) {
         HIP_OK(hipMemcpy(dq, q, sizeof(double) * size_t(n * R), hipMemcpyHostToDevice));
     } else {
@@ -1508,7 +1512,6 @@ fth_status fth_force(fth_ctx* c, const double* q, double* F) {
         for (size_t k = 0; k < t.size(); ++k) t[k] = float(q[k]);
         HIP_OK(hipMemcpy(dq, t.data(), sizeof(float) * t.size(), hipMemcpyHostToDevice));
         if (split) {
-            HIP_OK(hipMemset(dqt, 0, size_t(P * R) * 4));
             if (fth::launch_qt_from_q(static_cast<const float*>(dq), dqt, n, P, int32_t(R), c->stream) != 0)
                 return fail(FTH_EDEVICE, "q split launch failed");
         }

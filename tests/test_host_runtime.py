@@ -1,0 +1,115 @@
+"""The library's host code against a HIP runtime without a device
+(host_runtime.cpp, CPU): the order of its work on streams, its memory and its
+failure paths.  Each case runs in a child process that loads the stand-in
+runtime before the library; kernels are recorded, not run, so no result of a
+solve is looked at here."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+VERSIONS = """
+hip_4.2 { global: hip*; __hip*; stub_*; };
+hip_4.3 { global: hipGraphDestroy; hipGraphExecDestroy; hipGraphInstantiate; hipGraphLaunch;
+                  hipStreamBeginCapture; hipStreamEndCapture; } hip_4.2;
+"""
+
+PRELUDE = """
+import ctypes, os
+stub = ctypes.CDLL(os.environ["FTH_TEST_RUNTIME"], mode=ctypes.RTLD_GLOBAL)
+for name, res, args in (("stub_live", ctypes.c_size_t, []), ("stub_peak", ctypes.c_size_t, []),
+                        ("stub_host_live", ctypes.c_size_t, []), ("stub_limit", None, [ctypes.c_size_t]),
+                        ("stub_fail_in", None, [ctypes.c_long]), ("stub_mallocs", ctypes.c_long, []),
+                        ("stub_frees", ctypes.c_long, []), ("stub_launches", ctypes.c_long, []),
+                        ("stub_violations", ctypes.c_long, []), ("stub_violation", ctypes.c_char_p, [ctypes.c_long]),
+                        ("stub_logged", ctypes.c_long, []), ("stub_kernel", ctypes.c_char_p, [ctypes.c_long]),
+                        ("stub_reset", None, [])):
+    f = getattr(stub, name)
+    f.restype, f.argtypes = res, args
+import numpy as np
+import fth_inputs as fi
+from paper_1402_2095_amd import fth
+g = fi.load_gle("invsqrt_ns4")
+def no_violations():
+    v = [stub.stub_violation(k).decode() for k in range(stub.stub_violations())]
+    assert not v, (len(v), sorted(set(v))[:6])
+def kernels():
+    return [stub.stub_kernel(k).decode() for k in range(stub.stub_logged())]
+"""
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    d = tmp_path_factory.mktemp("host_runtime")
+    script, out = d / "versions", d / "libamdhip64.so.7"
+    script.write_text(VERSIONS)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-shared", "-fPIC", "-Wl,-soname,libamdhip64.so.7",
+                    f"-Wl,--version-script={script}", os.path.join(ROOT, "tests", "host_runtime.cpp"), "-o", str(out)],
+                   check=True)
+    return str(out)
+
+
+def run_child(runtime, code):
+    env = dict(os.environ, FTH_TEST_RUNTIME=runtime, PYTHONPATH=ROOT)
+    res = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(code) + "\nprint('child ok')"], env=env,
+                         capture_output=True, text=True, timeout=300, cwd=ROOT)
+    assert res.returncode == 0 and "child ok" in res.stdout, (res.stdout + res.stderr)[-4000:]
+
+
+SYSTEMS = """
+def systems():
+    M = fi.banded_spd_csr(700, 3)
+    D = fi.dense_ggt(700, 3)
+    S = fi.dense_ggt(60, 3)
+    for late in (False, True):   # the replica count given at create, or at the first run
+        yield M, 32, fth.FTH_FP32, late
+        yield M, 8, fth.FTH_FP64, late
+        yield S, 4, fth.FTH_FP64, late
+        yield D, 8, fth.FTH_FP32, late
+        yield D, 64, fth.FTH_FP32_BF16X3, late
+        yield fi.dense_ggt(2300, 3), 64, fth.FTH_FP32_BF16X3, late
+        yield D, 16, fth.FTH_FP64, late
+"""
+
+
+@pytest.mark.parametrize("trace", [0, 1])
+@pytest.mark.parametrize("tune", [0, 1])
+def test_work_waits_for_the_fills_it_needs(runtime, tune, trace):
+    """Buffers that start at zero (accumulators, step counter, state, trace
+    partials, a force call's scratch) are zero before a kernel runs."""
+    run_child(runtime, SYSTEMS + f"""
+for M, R, prec, late in systems():
+    kw = dict(pairs=fi.random_pairs(60, 20, 1), precision=prec, acc_diag=True, acc_pp=True, acc_trace=bool({trace}),
+              tune=bool({tune}))
+    sol = fth.Solver(M, g.A_p, g.C_p, 0.01, replicas=0 if late else R, **kw)
+    sol.run(70, R)
+    sol.read()
+    image = sol.save()
+    if prec != fth.FTH_FP32 and "quad" not in sol.kernel_name or "gemv" in sol.kernel_name:
+        if isinstance(M, np.ndarray):
+            sol.force(np.zeros((M.shape[0], R)))
+    sol.load(image)
+    sol.run(3)
+    sol.close()
+    no_violations()
+assert stub.stub_launches() > 1000
+""")
+
+
+@pytest.mark.parametrize("prec", ["FTH_FP32", "FTH_FP64"])
+def test_served_requests_wait_for_their_fills(runtime, prec):
+    run_child(runtime, f"""
+M = fi.banded_spd_csr(700, 3)
+srv = fth.Server(steps_per_tick=20)
+ids = [srv.submit(M=M, A_p=g.A_p, C_p=g.C_p, dt=0.01, pairs=fi.random_pairs(700, 20, 1), replicas=32,
+                  precision=fth.{prec}, seed=k, target=1e-9, max_steps=60) for k in range(3)]
+for _ in range(40):
+    srv.tick()
+assert all(srv.poll(i)["state"] == fth.FTH_REQ_DONE for i in ids)
+srv.close()
+no_violations()
+""")
