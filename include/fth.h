@@ -112,8 +112,10 @@ typedef struct {
 } fth_gle;
 
 /* Device memory provider (e.g. a framework's caching allocator).  alloc
- * returns device memory of at least `bytes` (NULL on failure); release gives
- * it back.  Both are called from the thread that calls into the library. */
+ * returns device memory of at least `bytes` (NULL on failure) that no work in
+ * flight uses: the library reads and writes it on streams of its own.  release
+ * gives it back, when those streams are done with it.  Both are called from the
+ * thread that calls into the library. */
 typedef struct {
     void* (*alloc)(size_t bytes, void* user);
     void (*release)(void* ptr, void* user);

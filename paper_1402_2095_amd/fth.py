@@ -76,12 +76,17 @@ class fth_allocator(ctypes.Structure):
 def torch_allocator():
     """An fth_allocator that takes device memory from PyTorch's caching
     allocator (the struct and its callbacks must be kept alive while a
-    context uses them)."""
+    context uses them).  A freed tensor's block may come back while kernels
+    of its stream still use it, which is in order on that stream only: the
+    library's work runs on others, so the block is handed on once PyTorch's
+    current stream has drained."""
     import torch
 
     def _alloc(nbytes, _user):
         try:
-            return int(torch.cuda.caching_allocator_alloc(int(nbytes)))
+            ptr = int(torch.cuda.caching_allocator_alloc(int(nbytes)))
+            torch.cuda.current_stream().synchronize()
+            return ptr
         except RuntimeError:
             return None
 

@@ -113,3 +113,20 @@ assert all(srv.poll(i)["state"] == fth.FTH_REQ_DONE for i in ids)
 srv.close()
 no_violations()
 """)
+
+
+def test_torch_memory_is_handed_on_when_its_stream_has_drained(monkeypatch):
+    """A block of PyTorch's caching allocator may still be in use by work
+    queued on its stream; the library uses it on other streams."""
+    import torch
+    from paper_1402_2095_amd import fth
+    events = []
+
+    class Stream:
+        def synchronize(self):
+            events.append("drained")
+
+    monkeypatch.setattr(torch.cuda, "caching_allocator_alloc", lambda n: events.append("taken") or 4096)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Stream())
+    assert fth.torch_allocator().alloc(100, None) == 4096
+    assert events == ["taken", "drained"]
