@@ -419,16 +419,11 @@ std::vector<double> dense_to_double(const fth_matrix* M) {
 constexpr int64_t kSmallMaxNR = 4096;       // n * R handled by one workgroup
 constexpr size_t kSmallMaxLds = 152 * 1024;  // LDS budget of the persistent kernel (160 KB per workgroup)
 
-fth_status ensure_state(fth_ctx* c, int32_t R) {
-    if (c->R != 0) {
-        if (R != 0 && R != c->R) return fail(FTH_ESTATE, "replica count is fixed at %d", c->R);
-        return FTH_OK;
-    }
-    if (R == 0) R = c->opt.replicas;
-    if (R == 0) return fail(FTH_EINVAL, "replica count not given");
+// M and the state of R replicas on the device (the part of ensure_state that may fail).
+fth_status lay_out_state(fth_ctx* c, int32_t R) {
     if (!is_pow2(R) || R > 512) return fail(FTH_EUNSUPPORTED, "R must be a power of two <= 512 (got %d)", R);
     int rpt = R >= 4 ? (R > 256 ? 8 : 4) : R;
-    if (c->dense() && !c->m_uploaded) {
+    if (c->dense()) {
         const int64_t threads = c->n * (R / std::min(R, 4));
         const size_t rb = c->real_bytes();
         const size_t lds_base = (size_t(c->n_out()) + 3) * 8 + 2 * size_t(c->n) * R * rb *
@@ -453,15 +448,6 @@ fth_status ensure_state(fth_ctx* c, int32_t R) {
             st2 = upload_dense(c);
         }
         if (st2 != FTH_OK) return st2;
-        c->m_src = nullptr;
-        c->m_host.clear();
-        c->m_host.shrink_to_fit();
-        c->m_uploaded = true;
-    } else if (c->mfma()) {
-        const bool few = R == 1 || R == 2 || R == 4 || R == 8;
-        if (c->gemv ? !few : (R != 16 && R != 32 && R != 64 && R != 128))
-            return fail(FTH_EUNSUPPORTED, "this dense context was set up for R in %s (got %d)",
-                        c->gemv ? "{1, 2, 4, 8}" : "{16, 32, 64, 128}", R);
     }
     c->R = R;
     c->rpt = rpt;
@@ -512,6 +498,40 @@ fth_status ensure_state(fth_ctx* c, int32_t R) {
     }
     HIP_OK(hipStreamSynchronize(c->stream));
     return FTH_OK;
+}
+
+fth_status ensure_state(fth_ctx* c, int32_t R) {
+    if (c->R != 0) {
+        if (R != 0 && R != c->R) return fail(FTH_ESTATE, "replica count is fixed at %d", c->R);
+        return FTH_OK;
+    }
+    if (R == 0) R = c->opt.replicas;
+    if (R == 0) return fail(FTH_EINVAL, "replica count not given");
+    const size_t held = c->allocs.size();
+    const fth_status st = lay_out_state(c, R);
+    if (st == FTH_OK) {  // the device holds the matrix now
+        c->m_src = nullptr;
+        c->m_host.clear();
+        c->m_host.shrink_to_fit();
+        return FTH_OK;
+    }
+    // Nothing of a failed attempt stays, so that the next one (of any R) starts afresh:
+    // kernels must not meet the buffers that were not allocated.
+    (void)hipStreamSynchronize(c->stream);
+    while (c->allocs.size() > held) {
+        c->raw_free(c->allocs.back());
+        c->allocs.pop_back();
+        c->alloc_bytes.pop_back();
+    }
+    c->R = c->rpt = c->rows_ct = 0;
+    c->small = c->small_quad = c->gemv = false;
+    c->rows_pad = 0;
+    c->ksplit = 1;
+    c->d_m_hi = c->d_msmall = c->d_part = nullptr;
+    c->d_qt = c->d_qt2 = nullptr;
+    for (int k = 0; k < 2; ++k) c->d_q[k] = c->d_ps[k] = nullptr;
+    for (void*& t : c->d_traj) t = nullptr;
+    return st;
 }
 
 template <typename Real>
@@ -691,6 +711,7 @@ fth_status trace_prepare(fth_ctx* c, int K) {
     HIP_OK(hipStreamSynchronize(c->stream));
     c->dfree(reinterpret_cast<void*&>(c->d_tpart));
     c->dfree(reinterpret_cast<void*&>(c->d_tsum));
+    c->tpart_k = c->tpart_w = 0;  // until both are there again
     const size_t pb = sizeof(double) * 3 * size_t(nk) * size_t(nw);
     HIP_OK(c->dalloc(reinterpret_cast<void**>(&c->d_tpart), pb));
     HIP_OK(hipMemsetAsync(c->d_tpart, 0, pb, c->stream));
@@ -793,7 +814,7 @@ fth_status tb_select(fth_ctx* c, int KT, int block) {
     return FTH_OK;
 }
 
-fth_status tb_prepare(fth_ctx* c) {
+fth_status tb_buffers(fth_ctx* c) {
     if (c->d_snap || c->d_pair_slot) return FTH_OK;
     const size_t rb = c->real_bytes();
     if (c->npairs > 0) {
@@ -825,6 +846,12 @@ void tb_release(fth_ctx* c) {
     c->tb_nslots = 0;
     c->tb_kt = 0;
     c->tbp_grid = 0;
+}
+
+fth_status tb_prepare(fth_ctx* c) {
+    const fth_status st = tb_buffers(c);
+    if (st != FTH_OK) tb_release(c);  // all of them or none
+    return st;
 }
 
 // Blocked launch j of a chunk: steps [j KT, j KT + KT) of it.

@@ -50,7 +50,6 @@ struct fth_ctx {
     const void* m_src = nullptr;
     bool m_src_f64 = false;
     std::vector<double> m_host;
-    bool m_uploaded = false;
     void* d_q[2] = {nullptr, nullptr};
     void* d_ps[2] = {nullptr, nullptr};  // p then s_1..s_ns, ping-pong by step parity,
                                          // rows grouped by 2^ps_lg (see ps_offset)

@@ -115,6 +115,61 @@ no_violations()
 """)
 
 
+@pytest.mark.parametrize("kind", ["create", "run"])
+def test_a_failed_allocation_leaves_nothing_behind(runtime, kind):
+    """Whichever device allocation of a context fails, the call reports it,
+    holds what it held before, and the next call allocates everything: no
+    kernel is launched on a buffer that is not there."""
+    run_child(runtime, SYSTEMS + f"""
+kind = {kind!r}
+for M, R, prec, late in systems():
+    if late != (kind == "run"):
+        continue
+    blocked = not isinstance(M, np.ndarray) and prec == fth.FTH_FP32
+    kw = dict(pairs=fi.random_pairs(60, 20, 1), precision=prec, acc_diag=True, acc_pp=True, acc_trace=True,
+              temporal_steps=3 if blocked else 0)
+    sol = fth.Solver(M, g.A_p, g.C_p, 0.01, replicas=0 if late else R, **kw)
+    sol.run(10, R)
+    want, name = sol.device_bytes, sol.kernel_name
+    sol.close()
+    k = 0
+    while True:
+        live = stub.stub_live()
+        if kind == "create":
+            stub.stub_fail_in(k)
+            try:
+                sol = fth.Solver(M, g.A_p, g.C_p, 0.01, replicas=R, **kw)
+                stub.stub_fail_in(-1)
+                break
+            except fth.FthError as e:
+                assert e.status == fth.FTH_ENOMEM, e
+            assert stub.stub_live() == live
+        else:
+            sol = fth.Solver(M, g.A_p, g.C_p, 0.01, **kw)
+            held = sol.device_bytes
+            stub.stub_fail_in(k)
+            try:
+                sol.run(10, R)
+                stub.stub_fail_in(-1)
+                break
+            except fth.FthError as e:
+                assert e.status == fth.FTH_ENOMEM, e
+            assert sol.device_bytes == held or k >= 4   # or: the state is there, a later buffer is not
+            # another replica count is open to a context without a state
+            if sol.device_bytes == held and k % 3 == 0 and R != 16 and prec != fth.FTH_FP32:
+                sol.run(10, 16)
+            else:
+                sol.run(10, R)
+                assert (sol.device_bytes, sol.kernel_name) == (want, name), (k, sol.device_bytes, want, sol.kernel_name)
+            sol.close()
+            assert stub.stub_live() == live
+        k += 1
+    assert k >= 5, k
+    sol.close()
+    assert stub.stub_live() == live
+""")
+
+
 def test_torch_memory_is_handed_on_when_its_stream_has_drained(monkeypatch):
     """A block of PyTorch's caching allocator may still be in use by work
     queued on its stream; the library uses it on other streams."""
