@@ -375,7 +375,10 @@ size_t fth_footprint_bytes(const fth_matrix* M, int32_t ns, int32_t replicas,
 typedef struct fth_server fth_server;
 
 typedef struct {
-    size_t hbm_budget;       /* bytes of device memory for requests; 0: 80% of free */
+    size_t hbm_budget;       /* bytes of device memory for requests; 0: 80% of free.  Memory of
+                                finished requests is kept for the next ones, at most 1 GiB and
+                                within this budget, until the server is destroyed or an
+                                allocation of its own fails */
     int32_t steps_per_tick;  /* steps between stderr checks (the chunk length
                                 at most); 0: 200 */
     int32_t max_active;      /* running requests at most; 0: 64 */

@@ -24,6 +24,7 @@
 #include <map>
 #include <memory>
 #include <thread>
+#include <type_traits>
 #include <vector>
 
 #include "fth_ctx.hpp"
@@ -91,60 +92,100 @@ struct Group {
 // Device memory of finished requests, kept for the next ones: a request's dozen
 // hipMalloc and hipFree calls (each free waits for the device) took up to 4 ms of its
 // life.  A context has waited for its stream before it gives a block back, so a block
-// may go to any other stream.  Bounded by kPoolBytes, given back when an allocation
-// fails and when the server goes; one pool per server, used by the server's caller only.
+// may go to any other stream.  What the pool holds beyond the bytes asked of it (idle
+// blocks, and the part of a reused block that its request did not ask for) stays within
+// `cap`: at most kPoolBytes, and what the requests' footprints leave of the budget.
+// Idle blocks are given back when an allocation fails and when the server goes; one
+// pool per server, used by the server's caller only.
 constexpr size_t kPoolBytes = size_t(1) << 30;
+constexpr size_t kPoolBlocks = 1024;  // blocks known at most (a search passes over all of them)
 
 struct DevicePool {
+    struct Block {
+        void* p;
+        size_t bytes, asked;  // asked: 0 while idle
+    };
     fth_allocator hook{};
-    std::multimap<size_t, void*> idle;  // by size
-    std::map<void*, size_t> size;       // of every block
-    size_t idle_bytes = 0;
+    std::vector<Block> blocks;
+    size_t idle = 0;      // bytes of idle blocks
+    size_t oversize = 0;  // bytes - asked of the blocks in use
+    size_t cap = kPoolBytes;
 
     DevicePool() {
         hook.alloc = [](size_t bytes, void* user) { return static_cast<DevicePool*>(user)->get(bytes); };
         hook.release = [](void* p, void* user) { static_cast<DevicePool*>(user)->put(p); };
         hook.user = this;
+        blocks.reserve(kPoolBlocks);  // no call below allocates host memory
     }
     DevicePool(const DevicePool&) = delete;
     DevicePool& operator=(const DevicePool&) = delete;
-    ~DevicePool() { drop(); }
+    ~DevicePool() { trim(0); }
 
+    // The smallest idle block that is at most a quarter too large, else new memory.
     void* get(size_t bytes) {
-        const size_t want = std::max<size_t>((bytes + 255) / 256 * 256, 256);
-        auto it = idle.lower_bound(want);
-        if (it != idle.end() && it->first <= want + want / 2) {  // no block more than half too large
-            void* p = it->second;
-            idle_bytes -= it->first;
-            idle.erase(it);
-            return p;
+        Block* best = nullptr;
+        bytes = std::max<size_t>(bytes, 1);
+        for (Block& b : blocks)
+            if (b.asked == 0 && b.bytes >= bytes && b.bytes <= bytes + std::max<size_t>(bytes / 4, 256) &&
+                (!best || b.bytes < best->bytes))
+                best = &b;
+        if (best) {
+            idle -= best->bytes;
+            oversize += best->bytes - bytes;
+            best->asked = bytes;
+            return best->p;
         }
         void* p = nullptr;
-        if (hipMalloc(&p, want) != hipSuccess) {
-            (void)hipGetLastError();
-            drop();
-            if (hipMalloc(&p, want) != hipSuccess) return nullptr;
+        if (!device_alloc(&p, bytes)) return nullptr;
+        if (blocks.size() == kPoolBlocks) {  // one idle block makes room, if there is one
+            for (size_t k = 0; k < blocks.size(); ++k)
+                if (blocks[k].asked == 0) {
+                    forget(k);
+                    break;
+                }
         }
-        size[p] = want;
-        return p;
+        if (blocks.size() < kPoolBlocks) blocks.push_back(Block{p, bytes, bytes});
+        return p;  // (a block that the list has no room for is freed when it comes back)
     }
     void put(void* p) {
-        const size_t b = size[p];
-        if (idle_bytes + b <= kPoolBytes) {
-            idle.emplace(b, p);
-            idle_bytes += b;
-        } else {
-            size.erase(p);
-            (void)hipFree(p);
+        for (size_t k = 0; k < blocks.size(); ++k) {
+            Block& b = blocks[k];
+            if (b.p != p) continue;
+            oversize -= b.bytes - b.asked;
+            b.asked = 0;
+            idle += b.bytes;
+            if (idle + oversize > cap) forget(k);
+            return;
         }
+        (void)hipFree(p);
     }
-    void drop() {
-        for (auto& kv : idle) {
-            size.erase(kv.second);
-            (void)hipFree(kv.second);
+    // Frees idle block k.
+    void forget(size_t k) {
+        idle -= blocks[k].bytes;
+        (void)hipFree(blocks[k].p);
+        blocks[k] = blocks.back();
+        blocks.pop_back();
+    }
+    // hipMalloc that takes the idle blocks back before it gives up.
+    bool device_alloc(void** p, size_t bytes) {
+        if (hipMalloc(p, bytes) == hipSuccess) return true;
+        (void)hipGetLastError();
+        if (idle > 0) {
+            trim(0);
+            if (hipMalloc(p, bytes) == hipSuccess) return true;
+            (void)hipGetLastError();
         }
-        idle.clear();
-        idle_bytes = 0;
+        *p = nullptr;
+        return false;
+    }
+    // Gives idle blocks back until idle + oversize <= bytes.
+    void trim(size_t bytes) {
+        for (size_t k = blocks.size(); k-- > 0 && idle > 0 && idle + oversize > bytes;)
+            if (blocks[k].asked == 0) forget(k);
+    }
+    void set_cap(size_t bytes) {
+        cap = std::min(bytes, kPoolBytes);
+        trim(cap);
     }
 };
 
@@ -168,6 +209,11 @@ struct fth_server {
     std::map<int, Group> groups;
     hipEvent_t ev_ref = nullptr;  // device-clock origin (recorded at creation)
 
+    // Reserves (or gives up) a request's footprint; the pool's idle memory gives way to it.
+    void reserve(int64_t bytes) {
+        reserved = size_t(int64_t(reserved) + bytes);
+        pool.set_cap(opt.hbm_budget > reserved ? opt.hbm_budget - reserved : 0);
+    }
     double clock() const {
         return std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     }
@@ -216,7 +262,13 @@ int64_t chunk_len(const fth_server* s, int64_t phase, double step_ms) {
 }
 
 fth_status group_upload(fth_server* s, Group& g) {
-    (void)s;
+    auto buffer = [&](auto** p, size_t bytes) -> fth_status {
+        void* m = nullptr;
+        if (!s->pool.device_alloc(&m, bytes)) return fail(FTH_ENOMEM, "no device memory for a packed group's work list");
+        *p = static_cast<std::remove_reference_t<decltype(**p)>*>(m);
+        return FTH_OK;
+    };
+    fth_status st;
     const int nslots = int(g.members.size());
     std::vector<fth::StepArgs<float>> table(size_t(std::max(nslots, 1)));
     std::vector<fth::PackedTile> tiles;
@@ -234,24 +286,29 @@ fth_status group_upload(fth_server* s, Group& g) {
         for (int64_t t = 0; t < pt; ++t) tiles.push_back(fth::PackedTile{k, 1, t});
     }
     if (int64_t(tiles.size()) > 0x7FFFFFFF) return fail(FTH_EUNSUPPORTED, "too many tiles in one packed group");
-    bool realloc = false;
     if (nslots > g.cap_slots) {
+        const int cap = std::max(2 * g.cap_slots, std::max(nslots, 8));
+        g.drop_graphs();  // they hold the buffer addresses
         (void)hipFree(g.d_table);
         g.d_table = nullptr;
-        g.cap_slots = std::max(2 * g.cap_slots, std::max(nslots, 8));
-        HIP_OK(hipMalloc(&g.d_table, sizeof(fth::StepArgs<float>) * size_t(g.cap_slots)));
-        realloc = true;
+        g.cap_slots = 0;
+        st = buffer(&g.d_table, sizeof(fth::StepArgs<float>) * size_t(cap));
+        if (st != FTH_OK) return st;
+        g.cap_slots = cap;
     }
     if (int64_t(tiles.size()) > g.cap_tiles) {
+        const int64_t cap = std::max<int64_t>(2 * g.cap_tiles, std::max<int64_t>(int64_t(tiles.size()), 1024));
+        g.drop_graphs();
         (void)hipFree(g.d_tiles);
         g.d_tiles = nullptr;
-        g.cap_tiles = std::max<int64_t>(2 * g.cap_tiles, std::max<int64_t>(int64_t(tiles.size()), 1024));
-        HIP_OK(hipMalloc(&g.d_tiles, sizeof(fth::PackedTile) * size_t(g.cap_tiles)));
-        realloc = true;
+        g.cap_tiles = 0;
+        st = buffer(&g.d_tiles, sizeof(fth::PackedTile) * size_t(cap));
+        if (st != FTH_OK) return st;
+        g.cap_tiles = cap;
     }
     if (!g.d_counts) {
-        HIP_OK(hipMalloc(&g.d_counts, 2 * sizeof(int32_t)));
-        realloc = true;
+        st = buffer(&g.d_counts, 2 * sizeof(int32_t));
+        if (st != FTH_OK) return st;
     }
     const int32_t counts[2] = {int32_t(tiles.size()), nslots};
     HIP_OK(hipMemcpyAsync(g.d_table, table.data(), sizeof(fth::StepArgs<float>) * size_t(nslots),
@@ -261,7 +318,6 @@ fth_status group_upload(fth_server* s, Group& g) {
                               g.stream));
     HIP_OK(hipMemcpyAsync(g.d_counts, counts, sizeof(counts), hipMemcpyHostToDevice, g.stream));
     HIP_OK(hipStreamSynchronize(g.stream));  // the host vectors die here
-    if (realloc) g.drop_graphs();            // the graphs bake the buffer addresses
     g.dirty = false;
     return FTH_OK;
 }
@@ -315,9 +371,9 @@ void finish(fth_server* s, SrvRequest* r, int32_t state, fth_status st) {
         r->est.assign(size_t(r->info.n_out), 0.0);
         r->se.assign(size_t(r->info.n_out), 0.0);
         if (state == FTH_REQ_DONE) (void)read_reported(r, r->est, r->se, nullptr);
+        s->reserve(-int64_t(r->info.footprint));
         fth_destroy(r->ctx);  // waits for its stream
         r->ctx = nullptr;
-        s->reserved -= r->info.footprint;
     }
     if (r->ev0) (void)hipEventDestroy(r->ev0);
     if (r->ev1) (void)hipEventDestroy(r->ev1);
@@ -338,16 +394,17 @@ void finish(fth_server* s, SrvRequest* r, int32_t state, fth_status st) {
 fth_status admit(fth_server* s, SrvRequest* r) {
     fth_ctx* c = nullptr;
     r->opt.allocator = &s->pool.hook;
+    s->reserve(int64_t(r->info.footprint));
     fth_status st = fth_create(&r->M, &r->gle, r->dt, r->pairs.empty() ? nullptr : r->pairs.data(),
                                int64_t(r->pairs.size() / 2), &r->opt, &c);
-    if (st != FTH_OK) return st;
-    r->ctx = c;
-    if (hipEventCreate(&r->ev0) != hipSuccess || hipEventCreate(&r->ev1) != hipSuccess) {
+    if (st == FTH_OK && (hipEventCreate(&r->ev0) != hipSuccess || hipEventCreate(&r->ev1) != hipSuccess))
+        st = fail(FTH_EDEVICE, "event creation failed");
+    if (st != FTH_OK) {
         fth_destroy(c);
-        r->ctx = nullptr;
-        return fail(FTH_EDEVICE, "event creation failed");
+        s->reserve(-int64_t(r->info.footprint));
+        return st;
     }
-    s->reserved += r->info.footprint;
+    r->ctx = c;
     r->info.t_start = s->clock();
     r->info.state = FTH_REQ_RUNNING;
     // the packed kernel runs 256-thread workgroups with 4 replicas per thread
@@ -683,7 +740,8 @@ fth_status fth_server_tick(fth_server* s) {
     // admission, in arrival order, while the footprint fits
     while (!s->queue.empty() && int(s->running.size()) < s->opt.max_active) {
         SrvRequest* r = s->queue.front();
-        if (s->reserved + r->info.footprint > s->opt.hbm_budget) break;
+        // (what reused blocks hold beyond their requests' needs is taken until those end)
+        if (s->reserved + r->info.footprint + s->pool.oversize > s->opt.hbm_budget) break;
         s->queue.pop_front();
         fth_status st = admit(s, r);
         if (st != FTH_OK) {

@@ -170,6 +170,81 @@ for M, R, prec, late in systems():
 """)
 
 
+SERVING = """
+def serve(srv, sizes, steps=60, prec=fth.FTH_FP32, R=32, until=fth.FTH_REQ_DONE, A=g.A_p, C=g.C_p):
+    ids = [srv.submit(M=fi.banded_spd_csr(n, 3), A_p=A, C_p=C, dt=0.01, pairs=fi.random_pairs(n, 20, 1),
+                      replicas=R, precision=prec, seed=n, target=1e-9, max_steps=steps) for n in sizes]
+    for _ in range(400):
+        srv.tick()
+        if all(srv.poll(i)["state"] >= fth.FTH_REQ_DONE for i in ids):
+            break
+    states = [srv.poll(i)["state"] for i in ids]
+    assert states == [until] * len(ids), states
+"""
+
+
+@pytest.mark.parametrize("budget_mb", [36, 64])
+def test_server_memory_stays_within_its_budget(runtime, budget_mb):
+    """What a server holds for running requests and keeps of finished ones is
+    within hbm_budget; without a budget to speak of it keeps at most 1 GiB."""
+    run_child(runtime, SERVING + f"""
+budget = {budget_mb} << 20
+extra = 1 << 20   # the work list of the packed group, rounding of requests
+srv = fth.Server(hbm_budget=budget, steps_per_tick=20, max_active=4)
+base = stub.stub_live()
+rng = np.random.default_rng(1)
+for k in range(12):
+    sizes = rng.integers(3000, 13000, 5)
+    for prec in (fth.FTH_FP32, fth.FTH_FP64):
+        serve(srv, sizes, prec=prec)
+    assert stub.stub_peak() - base <= budget + extra, (k, stub.stub_peak() - base, budget)
+    assert srv.stats()[2] == 0
+m = stub.stub_mallocs()
+serve(srv, sizes)
+serve(srv, sizes)
+assert stub.stub_mallocs() - m <= 5 * 16   # what the first of the two took serves the second
+srv.close()
+assert stub.stub_live() == base and stub.stub_host_live() == 0
+no_violations()
+""")
+
+
+def test_server_keeps_a_bounded_amount(runtime):
+    run_child(runtime, SERVING + """
+srv = fth.Server(steps_per_tick=20, max_active=2)
+for n in (130000, 260000, 520000):
+    serve(srv, [n], prec=fth.FTH_FP64)
+    assert stub.stub_live() <= (1 << 30) + (1 << 20), (n, stub.stub_live())
+assert stub.stub_live() > 1 << 28
+for n in range(200, 1400):   # many small sizes: the list of known blocks is bounded too
+    serve(srv, [n], steps=20, R=4)
+srv.close()
+assert stub.stub_live() == 0
+no_violations()
+""")
+
+
+@pytest.mark.parametrize("first", ["context", "group"])
+def test_an_allocation_that_fails_takes_idle_memory_back(runtime, first):
+    """Contexts and packed groups alike: a request is not refused for memory
+    that the server merely keeps."""
+    run_child(runtime, SERVING + f"""
+srv = fth.Server(steps_per_tick=20)
+if {first!r} == "context":   # idle memory of sizes that do not serve the next request
+    serve(srv, [40000], prec=fth.FTH_FP64)
+    stub.stub_limit(stub.stub_live() + (1 << 20))
+    serve(srv, [50000])
+else:   # idle blocks serve the request's context; the work list of its group (one per ns) is not there yet
+    serve(srv, [9000, 9000])
+    stub.stub_limit(stub.stub_live())
+    serve(srv, [9000], A=0.5 * np.eye(4), C=np.eye(4))
+assert stub.stub_live() > 0
+srv.close()
+assert stub.stub_live() == 0
+no_violations()
+""")
+
+
 def test_torch_memory_is_handed_on_when_its_stream_has_drained(monkeypatch):
     """A block of PyTorch's caching allocator may still be in use by work
     queued on its stream; the library uses it on other streams."""
