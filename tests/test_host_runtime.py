@@ -183,7 +183,7 @@ def serve(srv, sizes, steps=60, prec=fth.FTH_FP32, R=32, until=fth.FTH_REQ_DONE,
 """
 
 
-@pytest.mark.parametrize("budget_mb", [36, 64])
+@pytest.mark.parametrize("budget_mb", [44, 64])
 def test_server_memory_stays_within_its_budget(runtime, budget_mb):
     """What a server holds for running requests and keeps of finished ones is
     within hbm_budget; without a budget to speak of it keeps at most 1 GiB."""
