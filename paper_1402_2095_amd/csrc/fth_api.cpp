@@ -1116,6 +1116,39 @@ fth_status run_complete(fth_ctx* c, int64_t nsteps) {
     return FTH_OK;
 }
 
+size_t footprint_bytes(const fth_matrix* M, int32_t ns, int32_t R, int64_t npairs, int32_t acc_diag, int32_t precision,
+                       bool acc_pp) {
+    if (!M) return 0;
+    const size_t rb = precision == FTH_FP64 ? 8 : 4;
+    const size_t n = size_t(M->n);
+    // (p, s) rows are padded to whole groups of 128 / (R rb) rows (when R rb < 128)
+    const size_t grp = R > 0 && size_t(R) * rb < 128 ? 128 / (size_t(R) * rb) : 1;
+    const size_t ps_rows = (n + grp - 1) / grp * grp;
+    size_t bytes = 0;
+    if (M->format == FTH_CSR) {
+        bytes += (n + 1) * 8 + size_t(M->nnz) * (4 + rb);
+        bytes += n * size_t(R) * rb * 2 + 2 * ps_rows * size_t(R) * rb * size_t(1 + ns);
+    } else if ((R == 1 || R == 2 || R == 4 || R == 8) && int64_t(n) * R > kSmallMaxNR) {
+        const size_t ld = (n + 3) / 4 * 4;                                    // matrix-vector form
+        bytes += n * ld * rb;                                                  // M
+        bytes += 2 * ld * size_t(R) * rb + 2 * ps_rows * size_t(R) * rb * size_t(1 + ns);
+    } else {
+        const size_t P = size_t(dense_rows_pad(int64_t(n)));
+        const size_t ks = size_t(dense_ksplit(int64_t(P), precision));
+        bytes += P * P * (precision == FTH_FP32_BF16X3 ? 4 : rb);           // M (hi + lo, or FP64)
+        bytes += 2 * P * size_t(R) * rb + 2 * ps_rows * size_t(R) * rb * size_t(1 + ns);  // q, (p, s) pairs
+        const bool rows = dense_rows_cols(int64_t(n), R, precision) > 0;
+        if (!rows) bytes += ks * P * size_t(R) * rb;                           // split-K partials
+        if (precision == FTH_FP32_BF16X3) bytes += P * size_t(R) * (rows ? 8 : 4);  // bf16 q split(s)
+    }
+    if (M->format == FTH_DENSE && n <= size_t(fth::kSmallQuadRows) && R > 0 && R <= 64 && int64_t(n) * R <= kSmallMaxNR)
+        bytes += size_t(fth::kSmallQuadSteps) * n * size_t(R) * rb * (acc_pp ? 2 : 1);  // q (and p) of a chunk of steps
+    const size_t nout = (size_t(npairs) + (acc_diag ? n : 0)) * (acc_pp ? 2 : 1);
+    bytes += nout * 24 + size_t(npairs) * 8;
+    bytes += 2 * size_t(ns + 1) * size_t(ns + 1) * rb + 64;
+    return bytes;
+}
+
 template fth::StepArgs<float> step_args<float>(fth_ctx* c);
 template fth::StepArgs<double> step_args<double>(fth_ctx* c);
 
@@ -1147,35 +1180,7 @@ fth_status fth_propagator(const fth_gle* gle, double dt, double* T, double* S) {
 
 size_t fth_footprint_bytes(const fth_matrix* M, int32_t ns, int32_t R, int64_t npairs, int32_t acc_diag,
                            int32_t precision) {
-    if (!M) return 0;
-    const size_t rb = precision == FTH_FP64 ? 8 : 4;
-    const size_t n = size_t(M->n);
-    // (p, s) rows are padded to whole groups of 128 / (R rb) rows (when R rb < 128)
-    const size_t grp = R > 0 && size_t(R) * rb < 128 ? 128 / (size_t(R) * rb) : 1;
-    const size_t ps_rows = (n + grp - 1) / grp * grp;
-    size_t bytes = 0;
-    if (M->format == FTH_CSR) {
-        bytes += (n + 1) * 8 + size_t(M->nnz) * (4 + rb);
-        bytes += n * size_t(R) * rb * 2 + 2 * ps_rows * size_t(R) * rb * size_t(1 + ns);
-    } else if ((R == 1 || R == 2 || R == 4 || R == 8) && int64_t(n) * R > kSmallMaxNR) {
-        const size_t ld = (n + 3) / 4 * 4;                                    // matrix-vector form
-        bytes += n * ld * rb;                                                  // M
-        bytes += 2 * ld * size_t(R) * rb + 2 * ps_rows * size_t(R) * rb * size_t(1 + ns);
-    } else {
-        const size_t P = size_t(dense_rows_pad(int64_t(n)));
-        const size_t ks = size_t(dense_ksplit(int64_t(P), precision));
-        bytes += P * P * (precision == FTH_FP32_BF16X3 ? 4 : rb);           // M (hi + lo, or FP64)
-        bytes += 2 * P * size_t(R) * rb + 2 * ps_rows * size_t(R) * rb * size_t(1 + ns);  // q, (p, s) pairs
-        const bool rows = dense_rows_cols(int64_t(n), R, precision) > 0;
-        if (!rows) bytes += ks * P * size_t(R) * rb;                           // split-K partials
-        if (precision == FTH_FP32_BF16X3) bytes += P * size_t(R) * (rows ? 8 : 4);  // bf16 q split(s)
-    }
-    if (M->format == FTH_DENSE && n <= size_t(fth::kSmallQuadRows) && R > 0 && int64_t(n) * R <= kSmallMaxNR)
-        bytes += size_t(fth::kSmallQuadSteps) * n * size_t(R) * rb;            // trajectory of a chunk of steps
-    const size_t nout = size_t(npairs) + (acc_diag ? n : 0);
-    bytes += nout * 24 + size_t(npairs) * 8;
-    bytes += 2 * size_t(ns + 1) * size_t(ns + 1) * rb + 64;
-    return bytes;
+    return footprint_bytes(M, ns, R, npairs, acc_diag, precision, false);
 }
 
 fth_status fth_create(const fth_matrix* M_in, const fth_gle* gle_in, double dt, const int32_t* pairs, int64_t npairs,

@@ -210,6 +210,9 @@ fth_status ensure_state(fth_ctx* c, int32_t R);
 template <typename Real>
 fth::StepArgs<Real> step_args(fth_ctx* c);
 fth::StepLaunch step_launch(fth_ctx* c);
+// Device bytes of a context with these parameters (acc_pp: it keeps the momentum form too).
+size_t footprint_bytes(const fth_matrix* M, int32_t ns, int32_t R, int64_t npairs, int32_t acc_diag, int32_t precision,
+                       bool acc_pp);
 // Enqueue K steps (no graph) followed by the step-counter advance.
 fth_status enqueue_chunk(fth_ctx* c, int K);
 // Temporal blocking: whether the CSR system qualifies for KT steps per launch

@@ -711,9 +711,7 @@ fth_status fth_server_submit(fth_server* s, const fth_request* q, uint64_t* id) 
     std::vector<double> T, S;
     st = make_propagator(&r->gle, r->dt, T, S);
     if (st != FTH_OK) return st;
-    // (a momentum-form request keeps a second set of accumulators: counted as twice the pairs)
-    r->info.footprint = fth_footprint_bytes(&r->M, r->gle.ns, r->opt.replicas, q->npairs * (r->momentum ? 2 : 1), 0,
-                                            r->opt.precision);
+    r->info.footprint = footprint_bytes(&r->M, r->gle.ns, r->opt.replicas, q->npairs, 0, r->opt.precision, r->momentum);
     if (r->info.footprint > s->opt.hbm_budget)
         return fail(FTH_ENOMEM, "request footprint %zu exceeds the server budget %zu", r->info.footprint,
                     s->opt.hbm_budget);

@@ -245,6 +245,27 @@ no_violations()
 """)
 
 
+@pytest.mark.parametrize("momentum", [False, True])
+def test_a_request_holds_no_more_than_its_footprint(runtime, momentum):
+    run_child(runtime, f"""
+for M, R, prec in ((fi.banded_spd_csr(3000, 3), 32, fth.FTH_FP32), (fi.banded_spd_csr(3000, 3), 8, fth.FTH_FP64),
+                   (fi.dense_ggt(128, 3), 32, fth.FTH_FP64), (fi.dense_ggt(128, 3), 32, fth.FTH_FP32),
+                   (fi.dense_ggt(31, 3), 64, fth.FTH_FP32), (fi.dense_ggt(31, 3), 128, fth.FTH_FP64),
+                   (fi.dense_ggt(300, 3), 8, fth.FTH_FP64), (fi.dense_ggt(300, 3), 16, fth.FTH_FP32_BF16X3),
+                   (fi.dense_ggt(2300, 3), 64, fth.FTH_FP32_BF16X3), (fi.dense_ggt(1100, 3), 4, fth.FTH_FP32)):
+    n = M.shape[0] if isinstance(M, np.ndarray) else M.n
+    opt = dict(pairs=fi.random_pairs(n, 200, 1), replicas=R, precision=prec)
+    sol = fth.Solver(M, g.A_p, g.C_p, 0.01, acc_pp={momentum}, coded_matrix=-1, **opt)
+    held = sol.device_bytes
+    srv = fth.Server(steps_per_tick=20)
+    i = srv.submit(M=M, A_p=g.A_p, C_p=g.C_p, dt=0.01, target=1e-9, max_steps=600, momentum_form={momentum}, **opt)
+    # (fills of 256 bytes for arrays without elements are the only rounding)
+    assert held <= srv.poll(i)["footprint"] + 1024, (n, R, prec, held, srv.poll(i)["footprint"])
+    srv.close()
+    sol.close()
+""")
+
+
 def test_torch_memory_is_handed_on_when_its_stream_has_drained(monkeypatch):
     """A block of PyTorch's caching allocator may still be in use by work
     queued on its stream; the library uses it on other streams."""
