@@ -507,6 +507,7 @@ fth_status ensure_state(fth_ctx* c, int32_t R) {
     }
     if (R == 0) R = c->opt.replicas;
     if (R == 0) return fail(FTH_EINVAL, "replica count not given");
+    const device_scope on(c->device);  // memory and launches below go to the current device
     const size_t held = c->allocs.size();
     const fth_status st = lay_out_state(c, R);
     if (st == FTH_OK) {  // the device holds the matrix now
@@ -1409,7 +1410,7 @@ fth_status fth_read(fth_ctx* c, double* est, double* se, int64_t len, int64_t* n
     rs.samples = R * double(nacc);
     rs.blocks = double(nacc / c->opt.block_len);
     rs.per_block = 1.0 / (R * double(c->opt.block_len));
-    HIP_OK(hipSetDevice(c->device));
+    const device_scope on(c->device);
     HIP_OK(hipStreamSynchronize(c->stream));
     // Two chunks in flight: the device forms one while the host copies the other out.
     if (!c->h_read && no > 0) {

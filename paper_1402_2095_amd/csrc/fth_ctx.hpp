@@ -172,6 +172,19 @@ struct fth_ctx {
     }
 };
 
+// Makes a context's device current for a scope.
+struct device_scope {
+    int prev = -1;
+    explicit device_scope(int device) {
+        if (hipGetDevice(&prev) != hipSuccess || prev == device || hipSetDevice(device) != hipSuccess) prev = -1;
+    }
+    ~device_scope() {
+        if (prev >= 0) (void)hipSetDevice(prev);
+    }
+    device_scope(const device_scope&) = delete;
+    device_scope& operator=(const device_scope&) = delete;
+};
+
 // Scratch device memory for the duration of one call (freed on scope exit).
 struct ctx_scratch {
     fth_ctx* c;

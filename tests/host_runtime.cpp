@@ -72,6 +72,12 @@ void stub_reset() {
 void stub_fail_in(long n) { g_fail_in = n; }         // the n-th device allocation from now on (0: the next) fails
 void stub_limit(size_t bytes) { g_limit = bytes; }   // device memory there is (0: no limit)
 size_t stub_live() { return g_live; }
+size_t stub_live_on(int device) {
+    size_t n = 0;
+    for (const auto& m : g_mem)
+        if (m.second.second == device) n += m.second.first;
+    return n;
+}
 size_t stub_peak() { return g_peak; }
 size_t stub_host_live() { return g_host_live; }
 long stub_mallocs() { return g_mallocs; }

@@ -22,6 +22,7 @@ PRELUDE = """
 import ctypes, os
 stub = ctypes.CDLL(os.environ["FTH_TEST_RUNTIME"], mode=ctypes.RTLD_GLOBAL)
 for name, res, args in (("stub_live", ctypes.c_size_t, []), ("stub_peak", ctypes.c_size_t, []),
+                        ("stub_live_on", ctypes.c_size_t, [ctypes.c_int]),
                         ("stub_host_live", ctypes.c_size_t, []), ("stub_limit", None, [ctypes.c_size_t]),
                         ("stub_fail_in", None, [ctypes.c_long]), ("stub_mallocs", ctypes.c_long, []),
                         ("stub_frees", ctypes.c_long, []), ("stub_launches", ctypes.c_long, []),
@@ -263,6 +264,38 @@ for M, R, prec in ((fi.banded_spd_csr(3000, 3), 32, fth.FTH_FP32), (fi.banded_sp
     assert held <= srv.poll(i)["footprint"] + 1024, (n, R, prec, held, srv.poll(i)["footprint"])
     srv.close()
     sol.close()
+""")
+
+
+def test_the_device_of_a_context_and_of_its_caller(runtime):
+    """A context works on the device it was created on, whichever is current
+    later, and reading its results leaves the caller's device current."""
+    run_child(runtime, SYSTEMS + """
+hip = ctypes.CDLL("libamdhip64.so.7")
+def current():
+    d = ctypes.c_int()
+    hip.hipGetDevice(ctypes.byref(d))
+    return d.value
+for M, R, prec, late in systems():
+    assert hip.hipSetDevice(0) == 0
+    sol = fth.Solver(M, g.A_p, g.C_p, 0.01, pairs=fi.random_pairs(60, 20, 1), precision=prec, acc_trace=True,
+                     replicas=0 if late else R)
+    assert hip.hipSetDevice(1) == 0
+    sol.run(70, R)          # lays the state out when the replica count comes with the run
+    no_violations()
+    assert stub.stub_live_on(1) == 0
+    hip.hipSetDevice(1)
+    sol.read()
+    assert current() == 1
+    image = sol.save()
+    hip.hipSetDevice(0)
+    twin = fth.Solver(M, g.A_p, g.C_p, 0.01, pairs=fi.random_pairs(60, 20, 1), precision=prec, acc_trace=True)
+    hip.hipSetDevice(1)
+    twin.load(image)        # so does loading an image
+    assert current() == 1 and stub.stub_live_on(1) == 0
+    twin.close()
+    sol.close()
+    no_violations()
 """)
 
 
