@@ -367,8 +367,8 @@ size_t fth_footprint_bytes(const fth_matrix* M, int32_t ns, int32_t replicas,
  *  - a new request starts unpacked and joins its packed group at its next
  *    check boundary once the group is also at one;
  *  - at each check boundary the request's estimates and block stderrs are
- *    read (a few KB); it retires at its target (or max_steps), releasing its
- *    memory for the queue.
+ *    read (a few KB); it retires at its target (or max_steps, or the last check
+ *    boundary before step 2^32), releasing its memory for the queue.
  * A request's trajectory depends only on its own inputs (matrix, GLE, dt,
  * seed, stream_id, spectral map), and it stops at a check boundary, so its
  * result is the same alone and in any mix.  A server is not thread-safe. */

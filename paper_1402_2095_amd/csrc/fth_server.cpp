@@ -442,7 +442,9 @@ void check(fth_server* s, SrvRequest* r) {
     r->info.nblocks = nacc / r->opt.block_len;
     r->info.max_rel_stderr = max_rel_stderr(*r, est, se, r->info.nblocks, s->opt.min_blocks);
     const bool reached = r->info.max_rel_stderr <= r->target;
-    const bool capped = r->max_steps > 0 && r->info.steps >= r->max_steps;
+    // (the noise counters and the kernels' block arithmetic end at step 2^32, as in fth_run)
+    const bool capped = (r->max_steps > 0 && r->info.steps >= r->max_steps) ||
+                        r->info.steps + s->opt.steps_per_tick >= (int64_t(1) << 32);
     if (reached || capped) finish(s, r, FTH_REQ_DONE, FTH_OK);
 }
 

@@ -299,6 +299,21 @@ for M, R, prec, late in systems():
 """)
 
 
+def test_a_request_ends_before_step_2_to_the_32(runtime):
+    """Where fth_run refuses to go on: the noise counters would repeat."""
+    run_child(runtime, """
+M = fi.dense_ggt(129, 3)
+srv = fth.Server(steps_per_tick=1 << 30, quantum_ms=-1.0)
+i = srv.submit(M=M, A_p=g.A_p, C_p=g.C_p, dt=0.01, pairs=fi.random_pairs(129, 2, 1), replicas=4, precision=fth.FTH_FP64,
+               target=1e-30)
+for tick in range(4):
+    srv.tick()
+    if srv.poll(i)["state"] == fth.FTH_REQ_DONE:
+        break
+assert srv.poll(i)["state"] == fth.FTH_REQ_DONE and srv.poll(i)["steps"] == 3 << 30, srv.poll(i)
+""")
+
+
 def test_torch_memory_is_handed_on_when_its_stream_has_drained(monkeypatch):
     """A block of PyTorch's caching allocator may still be in use by work
     queued on its stream; the library uses it on other streams."""
