@@ -1384,6 +1384,26 @@ fth_status fth_set_steps_per_graph(fth_ctx* c, int32_t steps) {
     return FTH_OK;
 }
 
+// Not in the header: fixes the launch shape of a sparse context that the autotuner would
+// choose by time, so that each of its candidates can be run on its own.  The state must
+// be there; blocked schedules keep their own shape.
+fth_status fth_internal_step_shape(fth_ctx* c, int32_t threads, int32_t per_thread, int32_t streaming) {
+    if (!c) return fail(FTH_EINVAL, "ctx must not be NULL");
+    if (c->R == 0) return fail(FTH_ESTATE, "state not allocated (replica count not fixed)");
+    if (c->dense() || c->tb_kt > 0) return fail(FTH_EUNSUPPORTED, "only one-step sparse launches take a shape");
+    if ((threads != 64 && threads != 128 && threads != 256) || (per_thread != 2 && per_thread != 4 && per_thread != 8) ||
+        per_thread > c->R || c->R / per_thread > 64)
+        return fail(FTH_EINVAL, "no such launch shape for R = %d", c->R);
+    HIP_OK(hipStreamSynchronize(c->stream));
+    if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
+    c->gexec = nullptr;
+    c->block = threads;
+    c->rpt = per_thread;
+    c->nt = streaming != 0;
+    c->opt.tune = 0;
+    return FTH_OK;
+}
+
 int64_t fth_num_outputs(const fth_ctx* c) { return c ? c->n_out() : 0; }
 
 fth_status fth_get_accumulators(fth_ctx* c, double* blk, double* s1, double* s2, int64_t* nblocks, int64_t* step) {
