@@ -203,7 +203,8 @@ def unit_of(kernel_name: str):
                   r"dense_epilogue_kernel<(\w+),NS=(\d+),RPT=(\d+),NT=(\d)>", kernel_name)
     if m:
         gemm, rt, real, ns, rpt, nt = m.groups()
-        return "dense", [f"{gemm}<{rt}>", f"dense_epilogue_kernel<{real}, {ns}, {rpt}, "
+        end = "," if gemm == "gemm_f64_kernel" else ">"   # (the FP64 kernel's second argument: even K slices)
+        return "dense", [f"{gemm}<{rt}{end}", f"dense_epilogue_kernel<{real}, {ns}, {rpt}, "
                                           f"{'true' if nt == '1' else 'false'},"], 1
     m = re.search(r"(dense_rows_bf16x3_kernel|dense_rows_f64_kernel)<NS=(\d+),CT=(\d+)>", kernel_name)
     if m:

@@ -10,9 +10,9 @@
 // FP64 form (FTH_FP64): v_mfma_f64_16x16x4_f64 on M and q_n directly.
 //
 // Work split: the output rows are cut into row blocks and the k-steps that hold
-// columns into ksplit slices as even as they go (a power of two <= 8; padding is
-// neither read nor multiplied: 2300 rows at R = 64 15.3 -> 14.3 us a step, FP64 2100
-// rows at R = 128 61.6 -> 54.0); workgroup b takes K slice
+// columns into ksplit slices as even as they go (at most 8; padding is neither read
+// nor multiplied: 2300 rows at R = 64 15.3 -> 13.9 us a step, FP64 2100 rows at R = 128
+// 61.6 -> 50.8 with the epilogue at two replicas per thread); workgroup b takes K slice
 // b mod ksplit and row block b / ksplit.  The hardware deals workgroups
 // round-robin over the 8 XCDs, so the workgroups of K slice s run on the
 // XCDs x with x mod ksplit = s, and the q_n slice they stream stays in
@@ -192,7 +192,10 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16x3_kernel(const DenseGemmArgs
 }
 
 // ----------------------------------------------------------------- FP64 GEMM
-template <int RT>
+// EVEN: every slice has kslice columns.  With the general slice bounds the compiler orders
+// the loop's loads differently, which took 1 % of the step at 16384 rows, R = 128 (1078
+// against 1067 us); so where the slices are even their bounds stay plain.
+template <int RT, bool EVEN>
 __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(const DenseGemmArgs g) {
     constexpr int R = 16 * RT;
     constexpr int BM = 64;  // rows per workgroup: 4 waves x 16
@@ -205,7 +208,12 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(const DenseGemmArgs g)
     const int64_t m0 = rb * BM;
     int64_t kbeg;
     int nsteps;
-    gemm_kslice(g, ks, KS, kbeg, nsteps);
+    if constexpr (EVEN) {
+        kbeg = int64_t(ks) * g.kslice;
+        nsteps = int(g.kslice / KS);
+    } else {
+        gemm_kslice(g, ks, KS, kbeg, nsteps);
+    }
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     const int lr = l & 15, lg = l >> 4;
     const int64_t P = g.rows_pad;

@@ -119,6 +119,7 @@ struct DenseGemmArgs {
     int32_t R;
     int32_t ksplit;       // K slices
     int32_t kq, krem;     // (filled by the launchers) k-steps per slice, slices with one more
+    int64_t kslice;       // (FP64, filled by the launcher) columns per slice, where all have the same
 };
 
 // Largest workgroup of the temporally blocked step: a row's (p, s) and CSR

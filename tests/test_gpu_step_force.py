@@ -23,7 +23,9 @@ SPLIT, F32, F64 = fth.FTH_FP32_BF16X3, fth.FTH_FP32, fth.FTH_FP64
     (2310, 64, SPLIT, "gemm_bf16x3_kernel"),
     (271, 16, F64, "dense_rows_f64_kernel<NS=4,CT=1>"),
     (560, 128, F64, "dense_rows_f64_kernel<NS=4,CT=2>"),
-    (1260, 64, F64, "gemm_f64_kernel"),
+    (1260, 64, F64, "gemm_f64_kernel"),    # K slices of 16 and 15 k-steps
+    (1280, 64, F64, "gemm_f64_kernel"),    # all of 16
+    (2559, 32, F64, "gemm_f64_kernel"),    # all of 20, the last k-step not full
     (4099, 1, F32, "dense_gemv_kernel"),
     (515, 8, F64, "dense_gemv_kernel"),
     (100, 16, F32, "small_dense_kernel_quad"),
