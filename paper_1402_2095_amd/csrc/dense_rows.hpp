@@ -4,13 +4,15 @@
 // The split-K GEMM with its epilogue (dense.hpp) writes and reads partial sums and
 // pays two launches a step, which at a few thousand rows is most of the step, and
 // its 128-row blocks leave CUs idle there.  Here the eight waves of a workgroup take
-// the k-steps in turn, read A fragments of their 16 rows (each used by this
-// workgroup only) and the q fragments of 16 CT columns straight into registers, one
-// k-step ahead, and their partial sums meet in LDS in wave order.  The normals of
-// the rows are drawn between the first loads and their use and wait in LDS.  What
-// it costs is q: every workgroup reads all N rows of its columns from L2, N / 16
+// the k-steps in turn, read A fragments of their 16 rows (which the row block's other
+// column groups read too) and the q fragments of 16 CT columns straight into
+// registers, one k-step ahead, and their partial sums meet in LDS in wave order.  The
+// normals of the rows are drawn between the first loads and their use and wait in LDS.
+// What it costs is q: every workgroup reads all N rows of its columns from L2, N / 16
 // times N R values a step, so the GEMM form stays for large N R (see
-// dense_rows_cols).
+// dense_rows_cols).  M stays in the caches from step to step at these sizes, so its
+// loads are plain ones: non-temporal ones took 12.7 us a step for 10.1 (2100 rows,
+// R = 64), FP64 14.3 for 12.1 (1500 rows, R = 32), the same up to 1000 rows.
 //
 // Column groups: with CT < R / 16 a row block is cut into R / (16 CT) workgroups,
 // which puts small systems on more CUs.  A row's replicas are then spread over
@@ -186,7 +188,7 @@ __global__ __launch_bounds__(kRowsThreads) void dense_rows_bf16x3_kernel(const S
     auto load = [&](Frag& f, int kb) {
         const u32x4* ms = mt + int64_t(kb) * 2048;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) f.m[u] = __builtin_nontemporal_load(ms + u * 64);
+        for (int u = 0; u < 4; ++u) f.m[u] = ms[u * 64];
         const u32x4* q = qs + int64_t(kb) * 16 * R;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
@@ -265,8 +267,8 @@ __global__ __launch_bounds__(kRowsThreads) void dense_rows_f64_kernel(const Step
         double q[4][CT];
     };
     auto load = [&](Frag& f, int kb) {
-        f.m[0] = __builtin_nontemporal_load(reinterpret_cast<const f64x2*>(arow + int64_t(kb) * 16));
-        f.m[1] = __builtin_nontemporal_load(reinterpret_cast<const f64x2*>(arow + int64_t(kb) * 16 + 2));
+        f.m[0] = *reinterpret_cast<const f64x2*>(arow + int64_t(kb) * 16);
+        f.m[1] = *reinterpret_cast<const f64x2*>(arow + int64_t(kb) * 16 + 2);
         const double* qk = qcol + int64_t(kb) * 16 * R;
 #pragma unroll
         for (int t = 0; t < 4; ++t)
@@ -308,12 +310,15 @@ const void* rows_fn() {
         return reinterpret_cast<const void*>(&dense_rows_f64_kernel<NS, CT>);
 }
 
+// (four column tiles: n is beyond the FP64 form's range wherever they are chosen)
 template <typename Real, int NS>
 const void* pick_rows_ct(int ct) {
     switch (ct) {
         case 1: return rows_fn<Real, NS, 1>();
         case 2: return rows_fn<Real, NS, 2>();
-        case 4: return rows_fn<Real, NS, 4>();
+        case 4:
+            if constexpr (sizeof(Real) == 4) return rows_fn<Real, NS, 4>();
+            return nullptr;
         default: return nullptr;
     }
 }

@@ -309,16 +309,18 @@ int dense_ksplit(int64_t P, int prec) {
 }
 
 // 16-column tiles per workgroup of the one-launch dense step, 0 where the GEMM with its
-// epilogue is the faster form.  Every workgroup of the one-launch form reads its columns
-// of all of q_n from L2, n^2 R / 16 values a step at 16 rows each, against two launches
-// and the partial sums of the GEMM form.  Measured, us per step, one launch against GEMM:
-//   split form  n = 520 R = 64 4.6 / 10.8, 1000 R = 128 6.4 / 14.8, 2100 R = 64 13.0 / 15.1,
-//               4000 R = 16 15.2 / 15.9, 2100 R = 128 21.2 / 21.8, 4000 R = 32 19.3 / 17.7
-//   FP64        n = 520 R = 64 7.0 / 19.3, 1000 R = 64 10.2 / 19.8, 2100 R = 16 19.9 / 22.9,
-//               2100 R = 32 25.7 / 24.8
-// so the line lies at n^2 R = 3.2e8 (split) and 1e8 (FP64).  As few column tiles as keep
-// the launch within one workgroup per CU: more of them read M again, fewer leave CUs idle
-// (1000 rows, R = 64: 5.2 us with one tile, 252 workgroups; 7.0 with four, 63).
+// epilogue takes the step.  Every workgroup of the one-launch form reads its columns of
+// all of q_n from L2, n^2 R / 16 values a step at 16 rows each, against two launches and
+// the partial sums of the GEMM form.  Measured, us per step, one launch against GEMM:
+//   split form  n = 520 R = 64 4.4 / 10.0, 1000 R = 128 6.3 / 14.6, 1570 R = 128 9.4 / 17.6,
+//               2100 R = 64 10.2 / 13.5, 3000 R = 32 10.8 / 13.7, 4460 R = 16 19.4 / 21.7;
+//               past the line 3000 R = 64 14.9 / 16.5, 2100 R = 128 19.9 / 19.6
+//   FP64        n = 520 R = 64 6.7 / 14.5, 880 R = 128 12.2 / 25.3, 1250 R = 64 14.4 / 19.0,
+//               1760 R = 32 13.7 / 15.8, 2500 R = 16 17.4 / 20.7; past it 2100 R = 32 20.1 / 20.2
+// The two meet near n^2 R = 5.6e8 (split) and 1.4e8 (FP64); the lines, 3.2e8 and 1e8, lie
+// where the one-launch form is faster for every R.  As few column tiles as keep the launch
+// within one workgroup per CU: more of them read M again, fewer leave CUs idle
+// (1000 rows, R = 64: 5.1 us with one tile, 252 workgroups; 7.0 with four, 63).
 int dense_rows_cols(int64_t n, int R, int prec) {
     if (R != 16 && R != 32 && R != 64 && R != 128) return 0;
     if (double(n) * double(n) * R > (prec == FTH_FP64 ? 1.0e8 : 3.2e8)) return 0;
