@@ -1019,41 +1019,48 @@ fth_status autotune(fth_ctx* c) {
     // lattice 14^3, R = 16, 172 waves: 12.2 -> 10.5; at 843 waves it measured the same)
     const bool few_waves = c->n * c->R < int64_t(1024) * 256;
     const int rpts[3] = {4, 8, 2};
-    for (int b : blocks)
-        for (int rp : rpts)
-            for (int ntv = 0; ntv < 2; ++ntv) {
-                if (rp > c->R || c->R / rp > 64 || c->R / rp > b) continue;
-                if (rp == 2 && c->prec != FTH_FP64 && !few_waves) continue;
-                c->block = b;
-                c->rpt = rp;
-                c->nt = ntv != 0;
-                double us = 0.0;
-                fth_status st = time_chunk(c, 8, &us);
-                if (st != FTH_OK) return st;
-                if (us < best.us) best = TuneChoice{b, rp, ntv != 0, us, 0, 0};
-                if (rp == 4 && us < best4.us) best4 = TuneChoice{b, rp, ntv != 0, us, 0, 0};
-            }
-    if (try_tb && best4.us < 1e30) {
-        fth_status st = tb_prepare(c);
-        if (st != FTH_OK) return st;
-        c->block = best4.block;
-        c->rpt = 4;
-        c->nt = best4.nt;
-        const int kts[2] = {3, 5};
-        const int tbs[3] = {256, 512, 1024};
-        for (int kt : kts)
-            for (int tbb : tbs) {
-                if (!tb_eligible(c, kt, tbb)) continue;
-                st = tb_select(c, kt, tbb);
-                if (st != FTH_OK) return st;
-                double us = 0.0;
-                st = time_chunk(c, 2 * kt, &us);
-                if (st != FTH_OK) return st;
-                if (us < best.us) best = TuneChoice{best4.block, 4, best4.nt, us, kt, tbb};
-            }
-        c->tb_kt = 0;
-    }
+    const TuneChoice untuned = best;
+    auto sweep = [&]() -> fth_status {
+        for (int b : blocks)
+            for (int rp : rpts)
+                for (int ntv = 0; ntv < 2; ++ntv) {
+                    if (rp > c->R || c->R / rp > 64 || c->R / rp > b) continue;
+                    if (rp == 2 && c->prec != FTH_FP64 && !few_waves) continue;
+                    c->block = b;
+                    c->rpt = rp;
+                    c->nt = ntv != 0;
+                    double us = 0.0;
+                    fth_status st = time_chunk(c, 8, &us);
+                    if (st != FTH_OK) return st;
+                    if (us < best.us) best = TuneChoice{b, rp, ntv != 0, us, 0, 0};
+                    if (rp == 4 && us < best4.us) best4 = TuneChoice{b, rp, ntv != 0, us, 0, 0};
+                }
+        if (try_tb && best4.us < 1e30) {
+            fth_status st = tb_prepare(c);
+            if (st != FTH_OK) return st;
+            c->block = best4.block;
+            c->rpt = 4;
+            c->nt = best4.nt;
+            const int kts[2] = {3, 5};
+            const int tbs[3] = {256, 512, 1024};
+            for (int kt : kts)
+                for (int tbb : tbs) {
+                    if (!tb_eligible(c, kt, tbb)) continue;
+                    st = tb_select(c, kt, tbb);
+                    if (st != FTH_OK) return st;
+                    double us = 0.0;
+                    st = time_chunk(c, 2 * kt, &us);
+                    if (st != FTH_OK) return st;
+                    if (us < best.us) best = TuneChoice{best4.block, 4, best4.nt, us, kt, tbb};
+                }
+            c->tb_kt = 0;
+        }
+        return FTH_OK;
+    };
+    const fth_status swept = sweep();
+    if (swept != FTH_OK) best = untuned;  // the steps taken are undone all the same
     // restore
+    c->tb_kt = 0;
     for (int k = 0; k < 4; ++k) HIP_OK(hipMemcpyAsync(bufs[k], saved[k], sizes[k], hipMemcpyDeviceToDevice, c->stream));
     HIP_OK(hipMemcpyAsync(c->d_step, &step0, sizeof(int64_t), hipMemcpyHostToDevice, c->stream));
     HIP_OK(hipStreamSynchronize(c->stream));
@@ -1073,6 +1080,7 @@ fth_status autotune(fth_ctx* c) {
         (void)hipGraphExecDestroy(c->gexec);
         c->gexec = nullptr;
     }
+    if (swept != FTH_OK) return swept;
     tune_cache()[key] = best;
     return FTH_OK;
 }
