@@ -49,7 +49,8 @@ KERNEL_SOURCES = {
     "tbp": ["tbp_step.hpp", "tbp_step.hip", "tb_step.hpp", "row_update.hpp", "noise.hpp"],
     "dense": ["dense.hpp", "dense_f32.hip", "dense_f64.hip", "row_update.hpp", "noise.hpp"],
     "rows": ["dense_rows.hpp", "dense_rows_f32.hip", "dense_rows_f64.hip", "dense.hpp", "row_update.hpp", "noise.hpp"],
-    "gemv": ["dense_gemv.hpp", "dense_gemv_f32.hip", "row_update.hpp", "noise.hpp"],
+    "gemv": ["dense_gemv.hpp", "dense_gemv_f32.hip", "dense_gemv_f64.hip", "fth_internal.h", "row_update.hpp",
+             "noise.hpp"],
 }
 
 
