@@ -393,7 +393,7 @@ fth_status upload_small(fth_ctx* c) {
     return FTH_OK;
 }
 
-// Dense M for the few-replica force (R < 16): row-major in the state precision
+// Dense M for the few-replica force (R <= 8): row-major in the state precision
 // (FP32 for both FP32 forms), ld = n rounded up to 4, zero columns past n.
 fth_status upload_gemv(fth_ctx* c) {
     const int64_t n = c->n, ld = (n + 3) / 4 * 4;
@@ -637,7 +637,7 @@ fth::DenseGemmArgs gemm_args(fth_ctx* c, int k) {
     return g;
 }
 
-// The dense force partials of q_0 of g: the matrix-core GEMM, or for R < 16
+// The dense force partials of q_0 of g: the matrix-core GEMM, or for R <= 8
 // the matrix-vector form.
 int launch_force(const fth_ctx* c, const fth::DenseGemmArgs& g) {
     if (c->gemv)
