@@ -10,6 +10,7 @@
 #include <limits>
 #include <memory>
 #include <map>
+#include <new>
 #include <string>
 #include <tuple>
 #include <type_traits>
@@ -90,12 +91,15 @@ fth_status check_csr(const fth_matrix* M) {
     const double tol = (M->value_is_f64 ? 1e-12 : 1e-6) * vmax;
     // Rows are visited in order and columns increase, so the entries of row j meet their
     // mirror images (i, j) in order: next[j] is the first one not met yet.  (A search per
-    // entry took 1 ms of a 40000-row request's admission.)
-    std::vector<int64_t> next(M->row_ptr, M->row_ptr + n);
+    // entry took 1 ms of a 40000-row request's admission; it is left for when there is no
+    // memory for the cursors, which the checks themselves do not need.)
+    const std::unique_ptr<int64_t[]> next(new (std::nothrow) int64_t[size_t(n)]);
+    if (next) std::memcpy(next.get(), M->row_ptr, sizeof(int64_t) * size_t(n));
     for (int64_t i = 0; i < n; ++i) {
         for (int64_t k = M->row_ptr[i]; k < M->row_ptr[i + 1]; ++k) {
             const int32_t j = M->col[k];
-            const int64_t f = next[size_t(j)]++;
+            const int64_t f = next ? next[size_t(j)]++
+                                   : std::lower_bound(M->col + M->row_ptr[j], M->col + M->row_ptr[j + 1], int32_t(i)) - M->col;
             if (f >= M->row_ptr[j + 1] || M->col[f] != i)
                 return fail(FTH_EINVAL, "CSR pattern not symmetric at (%lld, %d)", (long long)i, j);
             if (std::fabs(val(f) - val(k)) > tol)

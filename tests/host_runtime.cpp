@@ -70,6 +70,7 @@ void stub_reset() {
     g_limit = 0;
 }
 void stub_fail_in(long n) { g_fail_in = n; }         // the n-th device allocation from now on (0: the next) fails
+void stub_devices(int n) { g_devices = n; }
 void stub_limit(size_t bytes) { g_limit = bytes; }   // device memory there is (0: no limit)
 size_t stub_live() { return g_live; }
 size_t stub_live_on(int device) {

@@ -24,6 +24,7 @@ stub = ctypes.CDLL(os.environ["FTH_TEST_RUNTIME"], mode=ctypes.RTLD_GLOBAL)
 for name, res, args in (("stub_live", ctypes.c_size_t, []), ("stub_peak", ctypes.c_size_t, []),
                         ("stub_live_on", ctypes.c_size_t, [ctypes.c_int]),
                         ("stub_host_live", ctypes.c_size_t, []), ("stub_limit", None, [ctypes.c_size_t]),
+                        ("stub_devices", None, [ctypes.c_int]),
                         ("stub_fail_in", None, [ctypes.c_long]), ("stub_mallocs", ctypes.c_long, []),
                         ("stub_frees", ctypes.c_long, []), ("stub_launches", ctypes.c_long, []),
                         ("stub_violations", ctypes.c_long, []), ("stub_violation", ctypes.c_char_p, [ctypes.c_long]),
@@ -311,6 +312,41 @@ for tick in range(4):
     if srv.poll(i)["state"] == fth.FTH_REQ_DONE:
         break
 assert srv.poll(i)["state"] == fth.FTH_REQ_DONE and srv.poll(i)["steps"] == 3 << 30, srv.poll(i)
+""")
+
+
+def test_validation_needs_no_host_memory_to_speak_of(runtime):
+    """A matrix that is there can be checked, also where no further array of
+    its rows' size fits the address space: the call goes on to its next step
+    (here, to find that there is no device) instead of ending the process."""
+    run_child(runtime, """
+import resource
+n = 10_000_000   # 80 MB of 64-bit cursors: never from the heap's free space
+val = np.full(3 * n, -1.0, dtype=np.float32)
+M = fi.CSR(n, np.zeros(n + 1, dtype=np.int64), np.zeros(3 * n - 2, dtype=np.int32), val[: 3 * n - 2])
+i = np.arange(n, dtype=np.int64)
+M.row_ptr[1:] = 3 * (i + 1) - 1
+M.row_ptr[n] = 3 * n - 2
+M.col[0:2] = (0, 1)
+M.col[2:] = (np.repeat(i[1:], 3) + np.tile([-1, 0, 1], n - 1))[: 3 * n - 4]
+M.val[0] = 3.0
+M.val[3::3] = 3.0
+del i
+stub.stub_devices(0)
+def status(m):
+    try:
+        fth.fth_create(m, [[1.0]], [[1.0]], 0.05, None, fth.fth_default_options())
+    except fth.FthError as e:
+        return e.status, str(e)
+assert status(M)[0] == fth.FTH_EDEVICE, status(M)
+used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used + (12 << 20), resource.RLIM_INFINITY))
+assert status(M)[0] == fth.FTH_EDEVICE, status(M)
+M.val[1] = -1.5
+assert status(M)[0] == fth.FTH_EINVAL and "not symmetric at (0, 1)" in status(M)[1], status(M)
+M.val[1] = -1.0
+M.col[4] = 7
+assert status(M)[0] == fth.FTH_EINVAL and "pattern not symmetric at (1, 7)" in status(M)[1], status(M)
 """)
 
 
